@@ -95,6 +95,24 @@ pd_status check_sigma_range(pd_basis b, bool product = true) {
 
 }  // namespace
 
+pd_status ensure_plan(pd_basis b, hipStream_t s, const WinPlan **plan) {
+    *plan = nullptr;
+    if (!b->plan_dev) return PD_OK;
+    if (!b->plan_ready) {
+        const size_t bytes = window_plan_bytes(b->omega, b->n);
+        std::unique_ptr<unsigned char[]> host(new (std::nothrow) unsigned char[bytes]());
+        if (!host) return fail(PD_ENOMEM, "host allocation failed");
+        if (!window_plan_build(b->omega, b->n, b->plan_dev, &b->plan, host.get()))
+            return fail(PD_EDEVICE, "the product's plan could not be built");
+        hipError_t e = hipMemcpyAsync(b->plan_dev, host.get(), bytes, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return fail(PD_EDEVICE, "plan upload: %s", hipGetErrorString(e));
+        b->plan_ready = 1;
+    }
+    *plan = &b->plan;
+    return PD_OK;
+}
+
 // Device memory check: turns host or foreign pointers, and device ranges that
 // run past the end of their allocation, into PD_EINVAL before any kernel runs.
 pd_status check_device_ptr(const void *p, const char *what, size_t bytes) {
@@ -216,6 +234,9 @@ pd_basis new_handle(void *dev_buf) {
     b->next_slot = 0;
     b->truncated = 0;
     std::memset(&b->trunc, 0, sizeof(b->trunc));
+    b->plan_dev = nullptr;
+    b->plan_ready = 0;
+    std::memset(&b->plan, 0, sizeof(b->plan));
     if (hipGetDevice(&b->device) != hipSuccess) b->device = 0;
     for (int i = 0; i < kSigmaSlots; ++i) {
         b->slot[i].dev = reinterpret_cast<CoefBlock *>(static_cast<unsigned char *>(dev_buf) + i * kCoefBytes);
@@ -362,7 +383,7 @@ int64_t pd_dimension(int omega, int n) {
 
 size_t pd_basis_bytes(int omega, int n, int store_states) {
     if (!valid_space(omega, n)) return 0;
-    size_t b = kHandleBlockBytes;
+    size_t b = kHandleBlockBytes + window_plan_bytes(omega, n);
     if (store_states) b += align256((size_t)binom_host(omega, n) * sizeof(uint64_t));
     return b;
 }
@@ -381,8 +402,11 @@ pd_status pd_basis_create(int omega, int n, int store_states, void *dev_buf, siz
     b->omega = omega;
     b->n = n;
     b->dim = (int64_t)binom_host(omega, n);
-    b->states = store_states ? reinterpret_cast<uint64_t *>(static_cast<unsigned char *>(dev_buf) + kHandleBlockBytes)
-                             : nullptr;
+    // after the coefficient blocks: the windowed product's plan, then the states
+    unsigned char *rest = static_cast<unsigned char *>(dev_buf) + kHandleBlockBytes;
+    const size_t plan_bytes = window_plan_bytes(omega, n);
+    if (plan_bytes) b->plan_dev = rest;
+    b->states = store_states ? reinterpret_cast<uint64_t *>(rest + plan_bytes) : nullptr;
     if (b->states) {
         hipError_t e = launch_basis_build(omega, n, b->dim, b->states, stream);
         if (e != hipSuccess) {
@@ -457,8 +481,10 @@ pd_status pd_sigma(pd_basis b, const double *eps, const double *V, pd_dtype dt, 
         if (e != hipSuccess) return fail(PD_EDEVICE, "coefficient upload: %s", hipGetErrorString(e));
         sl->has_coef = 1;
     }
+    const WinPlan *plan = nullptr;
+    if ((st = ensure_plan(b, stream, &plan)) != PD_OK) return st;
     hipError_t e = launch_sigma(b->omega, b->n, b->dim, sl->dev, dt, x_dev, y_dev, stream, blk.dsum64, blk.dsum32,
-                                trunc_of(b));
+                                trunc_of(b), plan);
     if (e == hipSuccess) e = hipEventRecord(sl->done, stream);
     if (e != hipSuccess) return fail(PD_EDEVICE, "sigma: %s", hipGetErrorString(e));
     sl->used = 1;

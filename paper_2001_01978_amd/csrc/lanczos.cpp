@@ -160,6 +160,12 @@ pd_status lanczos_run(pd_basis b, const CoefBlock &host_coef, const pd_lanczos_o
     const int omega = b->omega, n = b->n;
     const int64_t dim = b->dim;
     const TruncSpace *tr = b->truncated ? &b->trunc : nullptr;
+    const WinPlan *plan = nullptr;
+    {
+        std::lock_guard<std::mutex> lock(b->mu);
+        const pd_status st = ensure_plan(b, s, &plan);
+        if (st != PD_OK) return st;
+    }
     Layout L = layout_for(dim, o->krylov, o->precision);
     if (work_bytes < L.total)
         return fail(PD_ENOMEM, "workspace %zu bytes, need %zu", work_bytes, L.total);
@@ -256,7 +262,7 @@ pd_status lanczos_run(pd_basis b, const CoefBlock &host_coef, const pd_lanczos_o
                 PD_HIP(dev.fetch(kOffNrm, 1));
                 PD_HIP(launch_scale(w, dim, 1.0 / std::sqrt(dev.host[kOffNrm]), w, nullptr, s));
             }
-            PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, q, p, s, dsum64, dsum32, tr));
+            PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, q, p, s, dsum64, dsum32, tr, plan));
             ++info.iterations;
             const double one = 1.0, zero = 0.0;
             PD_HIP(launch_project(q, ld, 1, dim, p, false, 1.0, &one, &zero, partials, scal + kOffC, s));
@@ -305,10 +311,10 @@ pd_status lanczos_run(pd_basis b, const CoefBlock &host_coef, const pd_lanczos_o
             if (time_products) PD_HIP(hipEventRecord(ev.a, s));
             if (f32_step) {
                 PD_HIP(launch_sigma(omega, n, dim, coef, PD_F32, Q32 ? Q32 + (size_t)(k - 1) * ld : x32, y32, s,
-                                    dsum64, dsum32, tr));
+                                    dsum64, dsum32, tr, plan));
                 ++info.iterations_f32;
             } else {
-                PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, qk, p, s, dsum64, dsum32, tr));
+                PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, qk, p, s, dsum64, dsum32, tr, plan));
             }
             if (time_products) PD_HIP(hipEventRecord(ev.b, s));
             ++info.iterations;

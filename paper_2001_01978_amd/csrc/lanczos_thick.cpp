@@ -162,6 +162,12 @@ pd_status lanczos_eigs_run(pd_basis b, const CoefBlock &host_coef, int nev, cons
     const int omega = b->omega, n = b->n;
     const int64_t dim = b->dim;
     const TruncSpace *tr = b->truncated ? &b->trunc : nullptr;
+    const WinPlan *plan = nullptr;
+    {
+        std::lock_guard<std::mutex> lock(b->mu);
+        const pd_status st = ensure_plan(b, s, &plan);
+        if (st != PD_OK) return st;
+    }
     if (o->precision != PD_F64 && o->precision != PD_F32)
         return fail(PD_EINVAL, "several eigenpairs take precision PD_F64 or PD_F32");
     const TLayout L = tlayout(dim, o->krylov, o->precision);
@@ -247,10 +253,10 @@ pd_status lanczos_eigs_run(pd_basis b, const CoefBlock &host_coef, int nev, cons
         for (int j = kk; j < m; ++j) {
             double *qj = Q + (size_t)j * ld;
             if (f32) {
-                PD_HIP(launch_sigma(omega, n, dim, coef, PD_F32, x32, y32, s, dsum64, dsum32, tr));
+                PD_HIP(launch_sigma(omega, n, dim, coef, PD_F32, x32, y32, s, dsum64, dsum32, tr, plan));
                 ++info.iterations_f32;
             } else {
-                PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, qj, p, s, dsum64, dsum32, tr));
+                PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, qj, p, s, dsum64, dsum32, tr, plan));
             }
             const void *pin = f32 ? static_cast<const void *>(y32) : static_cast<const void *>(p);
             ++info.iterations;
@@ -365,7 +371,7 @@ pd_status lanczos_eigs_run(pd_basis b, const CoefBlock &host_coef, int nev, cons
         if (!(nrm > 0.0)) return fail(PD_EDEVICE, "Ritz vector %d vanished", i);
         const double sign = dev.host[kOffSum] < 0.0 ? -1.0 : 1.0;
         PD_HIP(launch_scale(u, dim, sign / nrm, u, nullptr, s));
-        PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, u, p, s, dsum64, dsum32, tr));
+        PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, u, p, s, dsum64, dsum32, tr, plan));
         ++info.iterations;
         const double one = 1.0, th = theta[i];
         PD_HIP(launch_project(Q + (size_t)i * ld, ld, 1, dim, p, false, 1.0, &one, &th, partials, scal + kOffC, s));

@@ -112,6 +112,72 @@ struct SigmaSlot {
     hipStream_t last_stream = nullptr;
     hipEvent_t done = nullptr;      // recorded after its last product
 };
+
+// ---------------------------------------------------------------- windowed product
+// (window_impl.h, window_plan.cpp.)  One class of lanes of a pass: the lanes of
+// workgroups first_block onwards, all with the same pair counts.
+struct WinClass {
+    uint32_t first_block, lanes;
+    uint32_t NL;      // states of nl pairs on the orbits below the window
+    uint32_t reach;   // largest rank count below the window that a lane reads
+    int32_t K, m, nl; // pairs in the window, above it, below it
+    int32_t pad;
+};
+struct WinPass {
+    const WinClass *cls;     // device
+    const int64_t *off;      // device: rank offset of each window state, per pair count
+    int nclass, W, w0, qmin;
+    uint32_t nblocks;
+};
+constexpr int kSegW = 7, kSegL = 9, kSeg = kSegW + kSegL;   // segment pass: window over low orbits
+constexpr int kSegGroup = 128;
+// Window pair counts in the order a group takes them, the longest lanes first.
+__host__ __device__ constexpr int seg_order(int t) {
+    return t < 6 ? (0x615243 >> (4 * t)) & 15 : t == 6 ? 0 : 7;
+}
+// The segments with q pairs, len elements each: nseg of them, in groups of
+// `group` numbered from `first` on.  items[t]: the end of the items (64 lanes
+// each) of window pair count seg_order(t); nl[K] low states, listed from
+// first_pat[K] on.  magic, lane_magic: e / len and f / nl[K] as the upper half
+// of a product (exact below 2^32 / len, 2^32 / nl[K]).
+struct SegClass {
+    uint32_t first, nseg;
+    int32_t q, len, group;
+    uint32_t magic;
+    int32_t items[kSegW + 1], nl[kSegW + 1], first_pat[kSegW + 1];
+    uint32_t lane_magic[kSegW + 1];
+};
+struct SegPass {
+    const SegClass *cls;     // device
+    const int32_t *off;      // device: place in the segment of each window state, per pair count
+    int nclass, qmin, cap;   // cap: elements of a group
+    uint32_t ngroup;
+};
+constexpr int kMaxWinPasses = 3;
+constexpr int kMaxWinOmega = 40;
+struct WinPlan {
+    SegPass seg;
+    WinPass pass[kMaxWinPasses];
+    int npass;
+};
+// Spaces whose products go by windows: at least kMinWinDim states and kMinWinPairs
+// pairs (or holes).  A lane does the work of up to C(W, K) rows, so a small space
+// leaves the chip idle, and with few pairs most lanes own one or two window
+// states.  Measured, row kernel against windows, us in FP64 / FP32: Omega = 23, n = 8
+// (490,314 states) 62 / 48 against 62 / 57; Omega = 22, n = 11 (705,432) 79 / 67
+// against 59 / 47; Omega = 40, n = 6 (3.8e6) 571 / 366 against 717 / 449, n = 7
+// (1.9e7) 2524 / 1465 against 2122 / 1231.
+constexpr uint64_t kMinWinDim = 600000;
+constexpr int kMinWinPairs = 7;
+// Bytes of a space's plan on the device, 0 when its products take a row per lane.
+size_t window_plan_bytes(int omega, int n);
+// The plan with device pointers into dev, and in host the window_plan_bytes
+// bytes to put there.
+bool window_plan_build(int omega, int n, void *dev, WinPlan *plan, unsigned char *host);
+hipError_t window_product_f64(const WinPlan &plan, int omega, int n, const double *d, const double *V,
+                              const double *x, double *y, hipStream_t s);
+hipError_t window_product_f32(const WinPlan &plan, int omega, int n, const float *d, const float *V, const float *x,
+                              float *y, hipStream_t s);
 }  // namespace pd
 
 struct pd_basis_s {
@@ -125,6 +191,9 @@ struct pd_basis_s {
     std::mutex mu;           // guards slot[] and next_slot (pd_sigma from several threads)
     int truncated;           // 1: dim = trunc.kept rows of a truncated space
     pd::TruncSpace trunc;
+    void *plan_dev;          // device bytes of the windowed product's plan, or nullptr
+    int plan_ready;          // the plan is built and on the device (guarded by mu)
+    pd::WinPlan plan;
 };
 
 namespace pd {
@@ -160,7 +229,11 @@ inline bool sigma_space_refused(int omega, int n) {
 bool sigma_launch_shape(int omega, int n, pd_dtype dt, int *threads, int64_t *lds, int64_t *limit);
 hipError_t launch_sigma(int omega, int n, int64_t dim, const CoefBlock *coef, pd_dtype dt,
                         const void *x, void *y, hipStream_t s, double dsum64, float dsum32,
-                        const TruncSpace *tr = nullptr);
+                        const TruncSpace *tr = nullptr, const WinPlan *plan = nullptr);
+// The plan of b's windowed product, put on the device first if this is its
+// first use (on stream s, which is then waited for); nullptr in *plan when b
+// has none.  Caller holds b->mu.
+pd_status ensure_plan(pd_basis b, hipStream_t s, const WinPlan **plan);
 
 // vec.hip: Lanczos vector kernels.  Q holds columns of length dim with leading
 // dimension ld (elements).  `partials` is scratch of partial_doubles() doubles.

@@ -24,7 +24,7 @@ hipError_t sigma_trunc_r64_f64(int, int, const TruncSpace &, const double *, con
                                double *, hipStream_t);
 
 hipError_t launch_sigma(int omega, int n, int64_t dim, const CoefBlock *coef, pd_dtype dt, const void *x, void *y,
-                        hipStream_t s, double dsum64, float dsum32, const TruncSpace *tr) {
+                        hipStream_t s, double dsum64, float dsum32, const TruncSpace *tr, const WinPlan *plan) {
     if (dim <= 0) return hipSuccess;
     const unsigned char *base = reinterpret_cast<const unsigned char *>(coef);  // device address
     if (tr) {
@@ -46,11 +46,13 @@ hipError_t launch_sigma(int omega, int n, int64_t dim, const CoefBlock *coef, pd
     if (dt == PD_F64) {
         const double *d = reinterpret_cast<const double *>(base + offsetof(CoefBlock, d64));
         const double *V = reinterpret_cast<const double *>(base + offsetof(CoefBlock, V64));
+        if (plan) return window_product_f64(*plan, omega, n, d, V, (const double *)x, (double *)y, s);
         return (small ? sigma_r32_f64 : sigma_r64_f64)(omega, n, dim, d, V, dsum64, (const double *)x, (double *)y, sched,
                                                      s);
     }
     const float *d = reinterpret_cast<const float *>(base + offsetof(CoefBlock, d32));
     const float *V = reinterpret_cast<const float *>(base + offsetof(CoefBlock, V32));
+    if (plan) return window_product_f32(*plan, omega, n, d, V, (const float *)x, (float *)y, s);
     return (small ? sigma_r32_f32 : sigma_r64_f32)(omega, n, dim, d, V, dsum32, (const float *)x, (float *)y, sched, s);
 }
 

@@ -1,0 +1,76 @@
+"""GPU: products of large full spaces, which go by orbit windows (window_impl.h).
+
+The spaces cover every window width (4 to 8 orbits), one, two and three
+windows, half-filled, sparse and mirrored fillings, and both sides of the
+rules that choose the product's kernels.  Inputs are dyadic (every product and
+partial sum exact), so results are compared with the oracle bit for bit.
+"""
+import math
+
+import numpy as np
+import pytest
+
+from paper_2001_01978_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+SPACES = [
+    (22, 11),            # the smallest: one window of 6
+    (23, 8),             # just below the smallest space: a row per lane
+    (23, 9), (23, 14),   # one window of 7
+    (24, 8), (24, 12),   # two windows of 4; one of 8
+    (24, 6),             # below the smallest number of pairs
+    (25, 9), (25, 16),   # windows of 5 and 4
+    (26, 7), (26, 19),   # two windows of 5, the fewest pairs
+    (27, 19),            # windows of 6 and 5
+    (29, 7),             # windows of 7 and 6
+    (31, 24),            # windows of 8 and 7
+    (33, 7),             # three windows (6, 6, 5), short segments in groups
+]
+
+
+@pytest.fixture(scope="module")
+def pdg():
+    import torch
+    from paper_2001_01978_amd import pairdiag
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    pairdiag.load()
+    return pairdiag
+
+
+@pytest.mark.parametrize("om,n", SPACES)
+def test_product_exact(pdg, oracle_mod, om, n):
+    import torch
+    _, _, eps, V = inputs.dyadic_instance(om, n, seed=om + n)
+    x = inputs.dyadic_vector(om, math.comb(om, n), bits=6)
+    want = oracle_mod.sigma(om, n, eps, V, oracle_mod.basis_alg1(om, n), x)
+    b = pdg.Basis(om, n, store_states=True)    # the states lie behind the plan in the handle's buffer
+    for dt in (torch.float64, torch.float32):
+        xt = torch.tensor(x, dtype=dt, device="cuda")
+        for _ in range(2):
+            y = torch.full_like(xt, float("nan"))
+            b.sigma(eps, V, xt, y)
+            assert np.array_equal(y.cpu().numpy().astype(np.float64), want), (dt, om, n)
+    got = b.states().cpu().numpy().view(np.uint64)
+    assert np.array_equal(got, oracle_mod.basis_alg1(om, n))
+
+
+def test_product_rounding(pdg, oracle_mod):
+    """Random inputs, an x that starts on any 8-byte (4-byte) boundary: within
+    the summation bound (hops + 2) u sum |H_ij x_j| of the oracle, every row."""
+    import torch
+    om, n = 23, 11
+    _, _, eps, V = inputs.c5_instance(om, n, seed=3)
+    d = math.comb(om, n)
+    x = inputs.random_vector(5, d)
+    basis = oracle_mod.basis_alg1(om, n)
+    b = pdg.Basis(om, n, store_states=False)
+    for dt, u in ((torch.float64, 2.0 ** -53), (torch.float32, 2.0 ** -24)):
+        xt = torch.empty(d + 1, dtype=dt, device="cuda")[1:]
+        xt.copy_(torch.tensor(x))
+        xd = xt.cpu().numpy().astype(np.float64)
+        want = oracle_mod.sigma(om, n, eps, V, basis, xd)
+        scale = oracle_mod.sigma(om, n, np.abs(eps), np.abs(V), basis, np.abs(xd))
+        y = b.sigma(eps, V, xt).cpu().numpy().astype(np.float64)
+        # (FP32 also rounds the couplings: one more u per term)
+        assert np.all(np.abs(y - want) <= (n * (om - n) + 4) * u * scale), dt
