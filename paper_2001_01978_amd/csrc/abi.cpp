@@ -318,7 +318,7 @@ MlpLayout mlp_layout(const pd_mlp_shape *s, int batch) {
     L.dL = take(B * s->out);
     L.G2 = take(B * s->h2);
     L.G1 = take(B * s->h1);
-    L.part = take(64);
+    L.part = take((size_t)mlp_loss_tiles(batch, s->out));
     L.loss = take(1);
     L.total = off;
     return L;
@@ -343,14 +343,71 @@ P mlp_split(const pd_mlp_shape *s, P base, P *W1, P *b1, P *W2, P *b2, P *W3, P 
     q += s->out;
     return q;
 }
+// A (B x K, row stride K) times W (K x N), plus bias.
+MlpGemm layer(int B, int N, int K, const float *A, const float *W, const float *bias, float *C) {
+    MlpGemm g;
+    std::memset(&g, 0, sizeof(g));
+    g.M = B;
+    g.N = N;
+    g.K = K;
+    g.A = A;
+    g.lda = K;
+    g.B = W;
+    g.ldb = N;
+    g.C = C;
+    g.ldc = N;
+    g.bias = bias;
+    return g;
+}
+// grad W (in x out) = A^T G, grad b = column sums of G, over B rows.
+MlpGemm weight_grad(int B, int in, int out, const float *A, const float *G, float *gW, float *gb) {
+    MlpGemm g = layer(in, out, B, A, G, nullptr, gW);
+    g.ta = 1;
+    g.lda = in;
+    g.colsum = gb;
+    return g;
+}
+// G W^T (B x in) times gelu'(Z).
+MlpGemm input_grad(int B, int in, int out, const float *G, const float *W, const float *Z, float *dst) {
+    MlpGemm g = layer(B, in, out, G, W, nullptr, dst);
+    g.tb = 1;
+    g.ldb = out;
+    g.mode = kMlpTimesGeluGrad;
+    g.aux = Z;
+    return g;
+}
+MlpGemmSet one(const MlpGemm &g) {
+    MlpGemmSet s;
+    std::memset(&s, 0, sizeof(s));
+    s.g[0] = g;
+    return s;
+}
+MlpGemmSet both(const MlpGemm &g, const MlpGemm &h) {
+    MlpGemmSet s = one(g);
+    s.g[1] = h;
+    return s;
+}
+// The forward pass; with a target also the loss' partial sums and dL = d loss / d logits.
 hipError_t mlp_forward_impl(const pd_mlp_shape *s, const float *P, const float *X, int B, unsigned char *w,
-                            const MlpLayout &L, float *logits, hipStream_t st) {
+                            const MlpLayout &L, float *logits, hipStream_t st, const float *target = nullptr) {
     const float *W1, *b1, *W2, *b2, *W3, *b3;
     mlp_split<const float *>(s, P, &W1, &b1, &W2, &b2, &W3, &b3);
     float *Z1 = (float *)(w + L.Z1), *H1 = (float *)(w + L.H1), *Z2 = (float *)(w + L.Z2), *H2 = (float *)(w + L.H2);
-    hipError_t e = launch_gemm_bf16(false, false, B, s->h1, s->in, X, s->in, W1, s->h1, Z1, s->h1, b1, 2, H1, st);
-    if (e == hipSuccess) e = launch_gemm_bf16(false, false, B, s->h2, s->h1, H1, s->h1, W2, s->h2, Z2, s->h2, b2, 2, H2, st);
-    if (e == hipSuccess) e = launch_gemm_bf16(false, false, B, s->out, s->h2, H2, s->h2, W3, s->out, logits, s->out, b3, 1, nullptr, st);
+    MlpGemm l1 = layer(B, s->h1, s->in, X, W1, b1, Z1), l2 = layer(B, s->h2, s->h1, H1, W2, b2, Z2);
+    MlpGemm l3 = layer(B, s->out, s->h2, H2, W3, b3, logits);
+    l1.mode = l2.mode = kMlpGelu;
+    l1.out2 = H1;
+    l2.out2 = H2;
+    if (target) {
+        l3.mode = kMlpLoss;
+        l3.aux = target;
+        l3.out2 = (float *)(w + L.dL);
+        l3.partial = (float *)(w + L.part);
+        l3.count = (float)(B * s->out);
+    }
+    hipError_t e = launch_mlp_gemms(one(l1), st);
+    if (e == hipSuccess) e = launch_mlp_gemms(one(l2), st);
+    if (e == hipSuccess) e = launch_mlp_gemms(one(l3), st);
     return e;
 }
 }  // namespace
@@ -842,8 +899,7 @@ pd_status pd_mlp_backward(const pd_mlp_shape *s, const float *params_dev, const 
     if ((st = check_device_ptr(loss_dev, "loss_dev", 4)) != PD_OK) return st;
     unsigned char *w = (unsigned char *)work_dev;
     float *Lg = (float *)(w + L.L), *dL = (float *)(w + L.dL);
-    hipError_t e = mlp_forward_impl(s, params_dev, X_dev, batch, w, L, Lg, stream);
-    if (e == hipSuccess) e = launch_mlp_loss(batch * s->out, Lg, target_dev, dL, (float *)(w + L.part), loss_dev, stream);
+    hipError_t e = mlp_forward_impl(s, params_dev, X_dev, batch, w, L, Lg, stream, target_dev);
     const float *W1, *b1, *W2, *b2, *W3, *b3;
     mlp_split<const float *>(s, params_dev, &W1, &b1, &W2, &b2, &W3, &b3);
     float *gW1, *gb1, *gW2, *gb2, *gW3, *gb3;
@@ -851,19 +907,17 @@ pd_status pd_mlp_backward(const pd_mlp_shape *s, const float *params_dev, const 
     float *Z1 = (float *)(w + L.Z1), *H1 = (float *)(w + L.H1), *Z2 = (float *)(w + L.Z2), *H2 = (float *)(w + L.H2);
     float *G2 = (float *)(w + L.G2), *G1 = (float *)(w + L.G1);
     const int B = batch;
-    // layer 3
-    if (e == hipSuccess) e = launch_gemm_bf16(true, false, s->h2, s->out, B, H2, s->h2, dL, s->out, gW3, s->out, nullptr, 0, nullptr, stream);
-    if (e == hipSuccess) e = launch_colsum(B, s->out, dL, gb3, stream);
-    if (e == hipSuccess) e = launch_gemm_bf16(false, true, B, s->h2, s->out, dL, s->out, W3, s->out, G2, s->h2, nullptr, 0, nullptr, stream);
-    if (e == hipSuccess) e = launch_gelu_back(B * s->h2, Z2, G2, stream);
-    // layer 2
-    if (e == hipSuccess) e = launch_gemm_bf16(true, false, s->h1, s->h2, B, H1, s->h1, G2, s->h2, gW2, s->h2, nullptr, 0, nullptr, stream);
-    if (e == hipSuccess) e = launch_colsum(B, s->h2, G2, gb2, stream);
-    if (e == hipSuccess) e = launch_gemm_bf16(false, true, B, s->h1, s->h2, G2, s->h2, W2, s->h2, G1, s->h1, nullptr, 0, nullptr, stream);
-    if (e == hipSuccess) e = launch_gelu_back(B * s->h1, Z1, G1, stream);
-    // layer 1
-    if (e == hipSuccess) e = launch_gemm_bf16(true, false, s->in, s->h1, B, X_dev, s->in, G1, s->h1, gW1, s->h1, nullptr, 0, nullptr, stream);
-    if (e == hipSuccess) e = launch_colsum(B, s->h1, G1, gb1, stream);
+    // a layer's weight gradients go with the gradient passed down, which reads the same
+    MlpGemmSet top = both(weight_grad(B, s->h2, s->out, H2, dL, gW3, gb3), input_grad(B, s->h2, s->out, dL, W3, Z2, G2));
+    top.partial = (const float *)(w + L.part);
+    top.npartial = mlp_loss_tiles(B, s->out);
+    top.scale = 1.0f / (float)(B * s->out);
+    top.loss = loss_dev;
+    if (e == hipSuccess) e = launch_mlp_gemms(top, stream);
+    if (e == hipSuccess)
+        e = launch_mlp_gemms(both(weight_grad(B, s->h1, s->h2, H1, G2, gW2, gb2),
+                                  input_grad(B, s->h1, s->h2, G2, W2, Z1, G1)), stream);
+    if (e == hipSuccess) e = launch_mlp_gemms(one(weight_grad(B, s->in, s->h1, X_dev, G1, gW1, gb1)), stream);
     if (e != hipSuccess) return fail(PD_EDEVICE, "mlp backward: %s", hipGetErrorString(e));
     return PD_OK;
 }

@@ -318,12 +318,34 @@ pd_status batched_run(int count, const int *omega, const int *n, const double *e
                       double *occ_out, pd_lanczos_info *info_out, pd_batch_info *binfo, hipStream_t stream);
 
 // mlp.hip
-hipError_t launch_gemm_bf16(bool ta, bool tb, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
-                            float *C, int ldc, const float *bias, int epilogue, float *H, hipStream_t s);
-hipError_t launch_mlp_loss(int count, const float *logits, const float *target, float *dl, float *partial,
-                           float *loss, hipStream_t s);
-hipError_t launch_gelu_back(int count, const float *z, float *g, hipStream_t s);
-hipError_t launch_colsum(int M, int N, const float *G, float *db, hipStream_t s);
+// C = op(A) op(B) (M x N over K, BF16 operands, FP32 sums): op(A)(m, k) = ta ? A[k*lda + m]
+// : A[m*lda + k], op(B)(k, n) = tb ? B[n*ldb + k] : B[k*ldb + n]; + bias[n] if
+// given.  M = 0: no product.  aux, out2: M x N with C's layout.
+enum { kMlpPlain = 0, kMlpGelu, kMlpLoss, kMlpTimesGeluGrad };
+struct MlpGemm {
+    int M, N, K;
+    const float *A, *B;
+    float *C;
+    int lda, ldb, ldc;
+    int ta, tb;
+    int mode;             // Gelu: out2 = gelu(C).  Loss: C = logits, aux = targets, out2 = d loss / d logits,
+                          // partial[tile] = sum of squares.  TimesGeluGrad: C = product * gelu'(aux)
+    const float *bias, *aux;
+    float *out2, *partial;
+    float *colsum;        // colsum[n] = sum_k op(B)(k, n), if given
+    float count;          // Loss: number of logits
+};
+// One or two products in one launch, and loss = scale * (sum of npartial partial sums) if loss is given.
+struct MlpGemmSet {
+    MlpGemm g[2];
+    int tiles[2];
+    const float *partial;
+    int npartial;
+    float scale;
+    float *loss;
+};
+hipError_t launch_mlp_gemms(MlpGemmSet set, hipStream_t s);
+int mlp_loss_tiles(int M, int N);
 hipError_t launch_adam(int count, float *p, const float *g, float *m, float *v, float lr, float b1, float b2,
                        float eps, int step, hipStream_t s);
 hipError_t launch_warm_expand(int omega, int n, int64_t dim, const float *logits, double lmax, double *psi,
