@@ -360,16 +360,18 @@ pd_status pd_occupations(pd_basis b, const double *psi_dev, void *work_dev, size
  * block: workgroup size 128, 256 or 512, or 0 to autotune it on a sample of the
  * batch (the choice is cached per batch shape for the life of the process;
  * batches of at most 32 instances, where the sample would be the whole batch,
- * take 512 untuned).  A cost model (work per product, team barrier overhead)
+ * take 512 untuned).  A cost model (work per product, a team's exchange overhead)
  * picks how many of the costliest instances are first solved by teams of
  * workgroups (grid = all compute units, split into 8 teams, or into the
  * smallest power of two of teams that covers them when fewer than 5 instances
- * go to teams) that split the rows and meet at a bounded-wait barrier; if a
+ * go to teams), how many of the next by teams of 8 workgroups (up to 2^18 states),
+ * and leaves the rest to single ones.  A team's members split the rows and
+ * meet in bounded waits; if a
  * wait times out (another kernel holding compute units) the call returns
  * PD_EDEVICE.  Without teams the grid is min(count, compute units).  The
  * workspace holds one Krylov slot of (krylov + 2) x (largest dimension)
- * doubles per team and one per workgroup sized for the largest instance left
- * to single workgroups (pd_batched_workspace_bytes): a batch that sends 5 or
+ * doubles per large team, one per team of 8 and one per workgroup, each sized for the
+ * largest instance that it may hold (pd_batched_workspace_bytes): a batch that sends 5 or
  * more instances to teams, the largest of 2.26e8 states (omega = 32, 12
  * pairs), needs 8 such slots, more than one device holds at krylov 20; solve
  * such instances with pd_lanczos_ground.  Returns PD_ENOCONV if any
@@ -380,9 +382,9 @@ typedef struct {
     int block;             /* workgroup size used */
     int grid;              /* persistent workgroups (one per compute unit; at most count without teams) */
     int tuned;             /* 1 if this call ran the autotuner */
-    int teams;             /* workgroup teams for the large instances (0: none) */
-    int team_size;         /* workgroups per team */
-    int large;             /* instances solved by teams */
+    int teams;             /* workgroup teams for the largest instances (0: none) */
+    int team_size;         /* workgroups per such team */
+    int large;             /* instances solved by them */
     int converged;         /* instances that met the tolerance */
     long long total_iterations;
     double tune_seconds;

@@ -31,7 +31,6 @@ namespace batched {
 constexpr int kMaxPairs = 12;    // min(n, omega - n) of a batched instance
 constexpr int kMaxOmegaB = 32;   // orbits of a batched instance
 constexpr int kMaxKrylovB = 32;  // Krylov vectors per cycle
-constexpr int kMaxWaves = 16;    // blocks of at most 1024 threads
 
 struct Instance {
     int omega, n, nn, comp;
@@ -55,18 +54,21 @@ struct Result {
 struct Args {
     const Instance *inst;
     int count;
-    int n_large;          // instances [0, n_large) of the sorted table are solved by teams
-    int teams;            // 0, or number of teams (the grid is teams * team_size workgroups)
-    int team_size;
-    int *counter;         // small-instance queue (starts at n_large)
-    int *large_counter;   // large-instance queue
-    int *team_ctl;        // per team: barrier count, generation, mailbox (each on its own 128-byte line)
-    double *team_part;    // per team: 2 buffers x 8 values x team_size partial sums
+    int *counter;         // queue of the instances left to single workgroups (from level[1].end on)
+    // The sorted table's first instances are solved by teams of workgroups: up to
+    // level[0].end by the large ones, up to level[1].end by those of kMidTeam.
+    struct Level {
+        int teams, team_size;   // the grid is teams * team_size workgroups (teams = 0: no instances)
+        int end;
+        int *counter;           // queue
+        int *flag;              // per team: one flag per member (Team::flag), zero at the start
+        double *part;           // per team: 2 buffers x team_size x kMaxSums partial sums
+        double *slots;          // per team: one slot
+        int64_t slot_doubles;
+    } level[2];
     int *error;           // set when a team barrier times out
     long long spin_limit;
     const double *coef;
-    double *slots;          // team slots (instances [0, n_large))
-    int64_t slot_doubles;
     double *slots2;         // one slot per workgroup for the rest
     int64_t slot2_doubles;
     double tol;
@@ -85,12 +87,12 @@ struct Shared {
     uint32_t Ct[kMaxOmegaB * (kMaxPairs + 2)];
     double Vs[kMaxOmegaB * kMaxOmegaB];
     double ds[kMaxOmegaB];
-    double scratch[kMaxWaves * 8];
+    double scratch[8 * (kMaxKrylovB + 2)];
     double alpha[kMaxKrylovB], beta[kMaxKrylovB], y[kMaxKrylovB];
     double c[kMaxKrylovB + 8], red[8];
     double sc[kMaxKrylovB + 1];   // column scales: q_j = sc[j] * (stored column j)
     double cs[kMaxKrylovB + 8];   // update coefficients of the stored columns
-    double A[kMaxKrylovB * kMaxKrylovB], v[kMaxKrylovB];
+    double A[3 * kMaxKrylovB], v[kMaxKrylovB];
     double theta;
     int idx, flag, abort;
 };
@@ -99,78 +101,87 @@ struct Shared {
 struct Team {
     int G, g;             // team size, member index
     int64_t r0, r1;       // rows owned by this member
-    int *ctl;             // barrier count at ctl[0], generation at ctl[32], mailbox at ctl[64]
-    double *part;         // 2 x 8 x G partial sums
+    int *flag;            // flag[q]: the last exchange that member q has entered
+    double *part;         // 2 x G x kMaxSums partial sums
     uint32_t *pre;        // the workgroup's per-lane LDS slots of the sigma
-    int parity;
+    int epoch;            // exchanges so far, the same for all members
+    int one_xcd;          // all members share an L2
 };
 
-constexpr int kCtlInts = 96;
+constexpr int kMaxSums = kMaxKrylovB + 2;
+// s_getreg operand of the hardware register XCC_ID (20): the wave's XCD, 4 bits from bit 0.
+constexpr int kXccId = 20 | (4 - 1) << 11;
 
-// Barrier over the team's workgroups.  Thread 0 of each member arrives on a
-// device-scope counter; the last one resets it and bumps the generation the
-// others spin on.  The spin is bounded: on timeout the error flag is raised
-// and every member abandons the instance, so the kernel always drains.
-__device__ bool team_sync(const Args &A, Team &T, Shared &sh) {
-    __syncthreads();
-    if (T.G == 1) return true;
-    if (threadIdx.x == 0) {
-        int *count = T.ctl, *gen = T.ctl + 32;
-        __threadfence();
-        const int g0 = atomicAdd(gen, 0);
-        int ok = 1;
-        if (atomicAdd(count, 1) == T.G - 1) {
-            atomicExch(count, 0);
-            __threadfence();
-            atomicAdd(gen, 1);
-        } else {
-            long long spins = 0;
-            while (atomicAdd(gen, 0) == g0) {
-                __builtin_amdgcn_s_sleep(2);
-                if (++spins > A.spin_limit || atomicAdd(A.error, 0) != 0) {
-                    atomicExch(A.error, 1);
-                    ok = 0;
-                    break;
-                }
-            }
-        }
-        __threadfence();
-        sh.abort = ok ? 0 : 1;
-    }
-    __syncthreads();
-    return sh.abort == 0;
+// Values that members pass to each other go past the caches that the XCDs do
+// not share, and are complete before the flag that announces them.
+__device__ __forceinline__ void put(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double get(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Sum NV per-thread values over the team; totals land in out[0..NV) of every member.
-template <int NV>
-__device__ __forceinline__ bool team_sum(const Args &A, Team &T, double (&v)[NV], Shared &sh, double *out) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-        double t = wave_sum(v[j]);
-        if (lane == 0) sh.scratch[wid * NV + j] = t;
-    }
+// Sums nv values over the team, in the order of its members: sh.scratch
+// [wave * kMaxSums + j] holds every wave's part, the totals land in out[0..nv)
+// of every member.  With VISIBLE everything the members wrote before is also
+// seen by all of them afterwards (a full barrier, nv may be 0).
+// Each member announces its sums with a flag of its own and waits for all
+// the others', so an exchange is one store and one load away; the fences, which
+// write an XCD's L2 back, are left to the exchanges that pass vectors on.
+// The wait is bounded: on a time-out the error flag is raised and every
+// member abandons the instance, so the kernel always drains.
+template <bool VISIBLE>
+__device__ bool team_exchange(const Args &A, Team &T, int nv, Shared &sh, double *out) {
+    const int tid = threadIdx.x, nw = blockDim.x >> 6;
     __syncthreads();
     double s = 0.0;
-    if ((int)threadIdx.x < NV) {
-        for (int w = 0; w < nw; ++w) s += sh.scratch[w * NV + threadIdx.x];
-        if (T.G == 1) out[threadIdx.x] = s;
-        else T.part[(T.parity * 8 + threadIdx.x) * T.G + T.g] = s;
-    }
+    if (tid < nv)
+        for (int w = 0; w < nw; ++w) s += sh.scratch[w * kMaxSums + tid];
     if (T.G == 1) {
+        if (tid < nv) out[tid] = s;
         __syncthreads();
         return true;
     }
-    if (!team_sync(A, T, sh)) return false;
-    if ((int)threadIdx.x < NV) {
-        const double *src = T.part + (T.parity * 8 + threadIdx.x) * T.G;
-        double t = 0.0;
-        for (int q = 0; q < T.G; ++q) t += src[q];
-        out[threadIdx.x] = t;
-    }
-    T.parity ^= 1;
+    const int epoch = ++T.epoch;
+    double *part = T.part + (int64_t)(epoch & 1) * T.G * kMaxSums;
+    if (tid < nv) put(part + (int64_t)T.g * kMaxSums + tid, s);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (tid == 0) sh.abort = 0;
     __syncthreads();
-    return true;
+    if (tid == 0) {
+        if (VISIBLE && !T.one_xcd) __threadfence();
+        __hip_atomic_store(T.flag + T.g, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    for (int q = tid; q < T.G; q += blockDim.x) {
+        long long spins = 0;
+        while (__hip_atomic_load(T.flag + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
+            __builtin_amdgcn_s_sleep(1);
+            if (++spins > A.spin_limit || ((spins & 63) == 0 && atomicAdd(A.error, 0) != 0)) {
+                atomicExch(A.error, 1);
+                sh.abort = 1;
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    if (VISIBLE) {
+        if (tid == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __syncthreads();
+    }
+    const bool ok = sh.abort == 0;
+    if (tid < nv) {
+        double t = 0.0;
+        for (int q = 0; q < T.G; ++q) t += get(part + (int64_t)q * kMaxSums + tid);
+        out[tid] = t;
+    }
+    __syncthreads();
+    return ok;
+}
+
+// Every wave's sum of v into sum j of the next exchange.
+__device__ __forceinline__ void put_sum(Shared &sh, int j, double v) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) sh.scratch[(threadIdx.x >> 6) * kMaxSums + j] = v;
 }
 
 template <int NN, bool COMP>
@@ -195,50 +206,112 @@ __device__ void wg_sigma(const Instance &I, const Team &T, const Shared &sh, con
     }
 }
 
-// c[j] = Q[j] . p for j < nc (c in LDS).  Every thread loads its 8 columns
-// together (indices clamped to the last column; c beyond nc is not used).
-__device__ bool wg_gemvt(const Args &A, Team &T, const double *Q, int64_t ld, int nc, const double *p, Shared &sh) {
-    for (int j0 = 0; j0 < nc; j0 += 8) {
-        double acc[8];
+// One step of put_sums: of v[0..2 H) a lane keeps half and passes the other half
+// on to its partner, OFF lanes away, which keeps that one.
+template <int H, int OFF>
+__device__ __forceinline__ double halve_sums(double (&v)[2 * H]) {
+    const bool up = (threadIdx.x & OFF) != 0;
+    double w[H];
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) acc[jj] = 0.0;
-        for (int64_t i = T.r0 + threadIdx.x; i < T.r1; i += blockDim.x) {
-            const double pi = p[i];
-            double q[8];
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) q[jj] = Q[(int64_t)(j0 + jj < nc ? j0 + jj : nc - 1) * ld + i];
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) acc[jj] += q[jj] * pi;
-        }
-        if (!team_sum<8>(A, T, acc, sh, sh.c + j0)) return false;
+    for (int i = 0; i < H; ++i) {
+        const double keep = up ? v[i + H] : v[i], pass = up ? v[i] : v[i + H];
+        w[i] = keep + __shfl_xor(pass, OFF, 64);
     }
-    return true;
+    if constexpr (H > 1) {
+        double (&half)[2 * (H / 2)] = w;
+        return halve_sums<H / 2, OFF / 2>(half);
+    } else {
+        double t = w[0];
+#pragma unroll
+        for (int o = OFF / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+        return t;
+    }
 }
 
-// p = sp * p - da * qa - db * qb in place (the recurrence terms known before
-// the projection); ||p||^2 after and ||sp * p||^2 to sh.red[0], sh.red[1].
-__device__ bool wg_shift(const Args &A, Team &T, double *p, double sp, const double *qa, double da,
-                         const double *qb, double db, Shared &sh) {
-    double acc[2] = {0.0, 0.0};
+// Every wave's sums of all[FIRST..FIRST + N) into those sums of the next exchange
+// (N a power of two).  Halving the number of values with every step takes about
+// N shuffles where a tree for each value takes 6 N.
+template <int N, int FIRST, int LEN>
+__device__ __forceinline__ void put_sums(Shared &sh, const double (&all)[LEN]) {
+    const int lane = threadIdx.x & 63;
+    double v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = all[FIRST + i];
+    const double t = halve_sums<N / 2, 32>(v);
+    if (lane % (64 / N) == 0) sh.scratch[(threadIdx.x >> 6) * kMaxSums + FIRST + lane / (64 / N)] = t;
+}
+
+// With ps = sp * p - da * qa - db * qb (the recurrence terms known before the
+// projection): p = ps, sh.c[j] = Q[j] . ps for j < nc <= N, then sh.c[N] = ||ps||^2 and
+// sh.c[N + 1] = ||sp * p||^2, all in one pass and one exchange.  Columns beyond nc repeat the last, so that all loads are unconditional.
+template <int N>
+__device__ __forceinline__ bool wg_project_n(const Args &A, Team &T, const double *Q, int64_t ld, int nc, double *p,
+                                          double sp, const double *qa, double da, const double *qb, double db,
+                                          Shared &sh) {
+    double acc[N], nrm[2] = {0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < N; ++j) acc[j] = 0.0;
     for (int64_t i = T.r0 + threadIdx.x; i < T.r1; i += blockDim.x) {
-        const double pf = sp * p[i];
-        const double ps = pf - da * qa[i] - db * qb[i];
+        double ps = p[i];
+        constexpr int H = N < 16 ? N : 16;
+        double q[H];
+        const double *qp = Q + i;
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+            q[j] = *qp;
+            qp += j + 1 < nc ? ld : 0;
+        }
+        const double pf = sp * ps;
+        ps = pf - da * qa[i] - db * qb[i];
         p[i] = ps;
-        acc[0] += ps * ps;
-        acc[1] += pf * pf;
+        nrm[0] += ps * ps;
+        nrm[1] += pf * pf;
+#pragma unroll
+        for (int j = 0; j < H; ++j) acc[j] += q[j] * ps;
+        if constexpr (N > H) {
+#pragma unroll
+            for (int j = H; j < N; ++j) {
+                q[j - H] = *qp;
+                qp += j + 1 < nc ? ld : 0;
+            }
+#pragma unroll
+            for (int j = H; j < N; ++j) acc[j] += q[j - H] * ps;
+        }
     }
-    return team_sum<2>(A, T, acc, sh, sh.red);
+    if constexpr (N == 24) {
+        put_sums<16, 0>(sh, acc);
+        put_sums<8, 16>(sh, acc);
+    } else {
+        put_sums<N, 0>(sh, acc);
+    }
+    put_sum(sh, N, nrm[0]);
+    put_sum(sh, N + 1, nrm[1]);
+    return team_exchange<false>(A, T, N + 2, sh, sh.c);
+}
+
+// The bound N of wg_project for nc columns.
+__device__ __forceinline__ int project_bound(int nc) { return nc <= 8 ? 8 : nc <= 16 ? 16 : nc <= 24 ? 24 : 32; }
+
+__device__ bool wg_project(const Args &A, Team &T, const double *Q, int64_t ld, int nc, double *p, double sp,
+                           const double *qa, double da, const double *qb, double db, Shared &sh) {
+    switch (project_bound(nc)) {
+        case 8: return wg_project_n<8>(A, T, Q, ld, nc, p, sp, qa, da, qb, db, sh);
+        case 16: return wg_project_n<16>(A, T, Q, ld, nc, p, sp, qa, da, qb, db, sh);
+        case 24: return wg_project_n<24>(A, T, Q, ld, nc, p, sp, qa, da, qb, db, sh);
+        default: return wg_project_n<32>(A, T, Q, ld, nc, p, sp, qa, da, qb, db, sh);
+    }
 }
 
 // out = p - sum_{j < nc} (q_j . p) q_j with q_j = sc_j Qt_j and the raw dot
-// products Qt_j . p in sh.c; ||out||^2 to sh.red[0].  out may equal p.
+// products Qt_j . p in sh.c; ||out||^2 to sh.red[0], and out is seen by the whole
+// team (it is the next product's input).  out may equal p.
 __device__ bool wg_update_to(const Args &A, Team &T, const double *Q, int64_t ld, int nc, const double *p,
                              double *out, Shared &sh) {
     if ((int)threadIdx.x < kMaxKrylovB + 8)
         sh.cs[threadIdx.x] = (int)threadIdx.x < nc ? sh.sc[threadIdx.x] * sh.sc[threadIdx.x] * sh.c[threadIdx.x]
                                                    : 0.0;
     __syncthreads();
-    double acc[1] = {0.0};
+    double acc = 0.0;
     for (int64_t i = T.r0 + threadIdx.x; i < T.r1; i += blockDim.x) {
         double v = p[i];
         for (int j0 = 0; j0 < nc; j0 += 8) {
@@ -249,18 +322,19 @@ __device__ bool wg_update_to(const Args &A, Team &T, const double *Q, int64_t ld
             for (int jj = 0; jj < 8; ++jj) v -= q[jj] * sh.cs[j0 + jj];
         }
         out[i] = v;
-        acc[0] += v * v;
+        acc += v * v;
     }
-    return team_sum<1>(A, T, acc, sh, sh.red);
+    put_sum(sh, 0, acc);
+    return team_exchange<true>(A, T, 1, sh, sh.red);
 }
 
-// out = a * in over the member's rows, then a team barrier (out is read whole next).
+// out = a * in over the member's rows, seen by the whole team (out is read whole next).
 __device__ bool wg_scale(const Args &A, Team &T, const double *in, double a, double *out, Shared &sh) {
     for (int64_t i = T.r0 + threadIdx.x; i < T.r1; i += blockDim.x) out[i] = a * in[i];
-    return team_sync(A, T, sh);
+    return team_exchange<true>(A, T, 0, sh, sh.red);
 }
 
-__device__ void solve_instance(const Args &A, const Instance &I, double *slot, Team T, Shared &sh) {
+__device__ void solve_instance(const Args &A, const Instance &I, double *slot, Team &T, Shared &sh) {
     const long long t_start = wall_clock64();
     const int omega = I.omega, ks = I.nn + 2;
     // stage tables (a barrier precedes any use)
@@ -291,7 +365,7 @@ __device__ void solve_instance(const Args &A, const Instance &I, double *slot, T
 
     // start: x_k = 2 u_k - 1 with u_k from SplitMix64 (seed, k)
     {
-        double acc[1] = {0.0};
+        double acc = 0.0;
         for (int64_t i = T.r0 + threadIdx.x; i < T.r1; i += blockDim.x) {
             uint64_t z = I.seed + (uint64_t)(i + 1) * 0x9E3779B97F4A7C15ull;
             z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
@@ -299,9 +373,10 @@ __device__ void solve_instance(const Args &A, const Instance &I, double *slot, T
             z = z ^ (z >> 31);
             double v = 2.0 * ((double)(z >> 11) * 0x1.0p-53) - 1.0;
             w[i] = v;
-            acc[0] += v * v;
+            acc += v * v;
         }
-        ok = team_sum<1>(A, T, acc, sh, sh.red) && wg_scale(A, T, w, 1.0 / sqrt(sh.red[0]), Q, sh);
+        put_sum(sh, 0, acc);
+        ok = team_exchange<false>(A, T, 1, sh, sh.red) && wg_scale(A, T, w, 1.0 / sqrt(sh.red[0]), Q, sh);
     }
 
     // Gram-Schmidt as in the single-instance solver: the recurrence terms
@@ -315,17 +390,17 @@ __device__ void solve_instance(const Args &A, const Instance &I, double *slot, T
     __syncthreads();
     for (cycle = 0; ok; ++cycle) {
         int m_eff = m;
+        double tnorm = 0.0;
         for (int k = 0; k < m; ++k) {
             const double *qk = Q + (int64_t)k * ld;
-            wg_sigma(I, T, sh, qk, p);
-            __syncthreads();
+            wg_sigma(I, T, sh, qk, p);   // p: the member's rows, each by the thread that reads it next
             ++iterations;
             const double sigma = k > 0 ? sh.alpha[k - 1] : theta;
             const double da = sigma * sh.sc[k];
             const double db = k > 0 ? sh.beta[k - 1] * sh.sc[k - 1] : 0.0;
-            if (!(ok = wg_shift(A, T, p, sh.sc[k], qk, da, k > 0 ? qk - ld : qk, db, sh))) break;
-            const double nrm_ps = sh.red[0], nrm_hq = sh.red[1];
-            if (!(ok = wg_gemvt(A, T, Q, ld, k + 1, p, sh))) break;
+            if (!(ok = wg_project(A, T, Q, ld, k + 1, p, sh.sc[k], qk, da, k > 0 ? qk - ld : qk, db, sh))) break;
+            const int at = project_bound(k + 1);
+            const double nrm_ps = sh.c[at], nrm_hq = sh.c[at + 1];
             const double alpha = sigma + sh.sc[k] * sh.c[k];
             const bool store = k + 1 < m;
             double nrm_v = 0.0;
@@ -334,7 +409,7 @@ __device__ void solve_instance(const Args &A, const Instance &I, double *slot, T
                 if (!(ok = wg_update_to(A, T, Q, ld, k + 1, p, out, sh))) break;
                 nrm_v = sh.red[0];
                 if (!(nrm_v >= kEta2 * nrm_ps && nrm_v >= kTau2 * nrm_hq)) {
-                    if (!(ok = wg_gemvt(A, T, Q, ld, k + 1, out, sh))) break;
+                    if (!(ok = wg_project(A, T, Q, ld, k + 1, out, 1.0, out, 0.0, out, 0.0, sh))) break;
                     if (!(ok = wg_update_to(A, T, Q, ld, k + 1, out, out, sh))) break;
                     nrm_v = sh.red[0];
                 }
@@ -353,9 +428,7 @@ __device__ void solve_instance(const Args &A, const Instance &I, double *slot, T
                 if (converged || final_check) break;
             }
             if (!store) break;
-            double tnorm = 0.0;
-            __syncthreads();
-            for (int i = 0; i <= k; ++i) tnorm = fmax(tnorm, fabs(sh.alpha[i]) + sh.beta[i]);
+            tnorm = fmax(tnorm, fabs(alpha) + beta);
             if (beta <= 1e-14 * fmax(tnorm, 1e-300)) {
                 m_eff = k + 1;
                 break;
@@ -363,21 +436,26 @@ __device__ void solve_instance(const Args &A, const Instance &I, double *slot, T
         }
         if (!ok || converged || final_check) break;
         __syncthreads();
-        if (threadIdx.x == 0)
-            sh.flag = tridiag_lowest_work(m_eff, sh.alpha, sh.beta, &sh.theta, sh.y, sh.A, sh.v);
+        if (threadIdx.x < 64) {
+#ifdef __HIP_DEVICE_COMPILE__
+            const int st = tridiag_lowest_wave(m_eff, sh.alpha, sh.beta, &sh.theta, sh.y, sh.A, sh.v);
+            if (threadIdx.x == 0) sh.flag = st;
+#endif
+        }
         __syncthreads();
         if (sh.flag != 0) break;
         theta = sh.theta;
         // psi = Q y, normalised, becomes q_1
         {
-            double acc[1] = {0.0};
+            double acc = 0.0;
             for (int64_t i = T.r0 + threadIdx.x; i < T.r1; i += blockDim.x) {
                 double v = 0.0;
                 for (int j = 0; j < m_eff; ++j) v += Q[(int64_t)j * ld + i] * (sh.y[j] * sh.sc[j]);
                 w[i] = v;
-                acc[0] += v * v;
+                acc += v * v;
             }
-            ok = team_sum<1>(A, T, acc, sh, sh.red) && wg_scale(A, T, w, 1.0 / sqrt(sh.red[0]), Q, sh);
+            put_sum(sh, 0, acc);
+            ok = team_exchange<false>(A, T, 1, sh, sh.red) && wg_scale(A, T, w, 1.0 / sqrt(sh.red[0]), Q, sh);
         }
         if (threadIdx.x == 0) sh.sc[0] = 1.0;
         __syncthreads();
@@ -404,7 +482,9 @@ __device__ void solve_instance(const Args &A, const Instance &I, double *slot, T
 #pragma unroll
             for (int jj = 0; jj < 8; ++jj) acc[jj] += ((s >> (i0 + jj)) & 1ull) ? wq : 0.0;
         }
-        if (!(ok = team_sum<8>(A, T, acc, sh, sh.red))) break;
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) put_sum(sh, jj, acc[jj]);
+        if (!(ok = team_exchange<false>(A, T, 8, sh, sh.red))) break;
         if (T.g == 0 && (int)threadIdx.x < 8 && i0 + (int)threadIdx.x < omega)
             A.occ[I.occ_off + i0 + threadIdx.x] = 2.0 * sh.red[threadIdx.x];
         __syncthreads();
@@ -430,42 +510,58 @@ inline size_t batched_dyn_lds(int block) { return (size_t)2 * (kMaxPairs + 1) * 
 __global__ __launch_bounds__(512) void batched_kernel(Args A) {
     __shared__ Shared sh;
     extern __shared__ __align__(16) unsigned char bdyn[];
-    // Phase 1 (teams > 0): large instances, one team of workgroups each
-    // (team = workgroup id mod teams, member = id / teams, all members work in
-    // the slot of member 0).  Phase 2: the rest, one workgroup each.  A single
-    // call site of solve_instance keeps one copy of the solver in the kernel.
+    // Levels 0 and 1: instances solved by a team of workgroups each (team =
+    // workgroup id mod teams, member = id / teams: the members of a smaller team
+    // all come from one larger team, and workgroup ids that are equal modulo 8 lie on
+    // one XCD).  Level 2: the rest, one workgroup each.  A single call site of
+    // solve_instance keeps one copy of the solver in the kernel.
     Team T;
     T.pre = reinterpret_cast<uint32_t *>(bdyn);
-    int phase = A.teams > 0 ? 1 : 2;
-    const int t = A.teams > 0 ? (int)(blockIdx.x % A.teams) : 0;
+    T.epoch = 0;
+    T.one_xcd = 0;
+    int level = 0;
     for (;;) {
         int idx;
         double *slot;
-        if (phase == 1) {
-            T.G = A.team_size;
-            T.g = blockIdx.x / A.teams;
-            T.ctl = A.team_ctl + t * kCtlInts;
-            T.part = A.team_part + (int64_t)t * 16 * A.team_size;
-            T.parity = 0;
-            if (T.g == 0 && threadIdx.x == 0) atomicExch(T.ctl + 64, atomicAdd(A.large_counter, 1));
-            if (!team_sync(A, T, sh)) break;
-            if (threadIdx.x == 0) sh.idx = atomicAdd(T.ctl + 64, 0);
-            __syncthreads();
-            // uniform across the workgroup: keep it (and the instance record) in scalar registers
-            idx = __builtin_amdgcn_readfirstlane(sh.idx);
-            // everyone has read the mailbox before member 0 may overwrite it
-            if (!team_sync(A, T, sh)) break;
-            if (idx >= A.n_large) {
-                phase = 2;
+        if (level < 2) {
+            const Args::Level &L = A.level[level];
+            if (L.teams == 0) {
+                ++level;
                 continue;
             }
-            slot = A.slots + (int64_t)t * A.slot_doubles;
+            const int t = blockIdx.x % L.teams;
+            T.G = L.team_size;
+            T.g = blockIdx.x / L.teams;
+            T.flag = L.flag + (int64_t)t * L.team_size;
+            T.part = L.part + (int64_t)t * 2 * L.team_size * kMaxSums;
+            // Member 0 takes the next instance and tells the others (the sum has no
+            // other terms); whether they all run on one XCD is told by the mean and
+            // the mean square of their XCD numbers.
+            for (int w = threadIdx.x; w < (int)(blockDim.x >> 6); w += blockDim.x) {
+                const int xcd = __builtin_amdgcn_s_getreg(kXccId);
+                double *sum = sh.scratch + w * kMaxSums;
+                sum[0] = T.g == 0 && w == 0 ? (double)atomicAdd(L.counter, 1) : 0.0;
+                sum[1] = w == 0 ? (double)xcd : 0.0;
+                sum[2] = w == 0 ? (double)(xcd * xcd) : 0.0;
+            }
+            T.one_xcd = 0;
+            if (!team_exchange<false>(A, T, 3, sh, sh.red)) break;
+            T.one_xcd = __builtin_amdgcn_readfirstlane(T.G * sh.red[2] == sh.red[1] * sh.red[1] ? 1 : 0);
+            // uniform across the workgroup: keep it (and the instance record) in scalar registers
+            idx = __builtin_amdgcn_readfirstlane((int)sh.red[0]);
+            __syncthreads();
+            if (idx >= L.end) {
+                ++level;
+                T.epoch = 0;
+                continue;
+            }
+            slot = L.slots + (int64_t)t * L.slot_doubles;
         } else {
             T.G = 1;
             T.g = 0;
-            T.ctl = nullptr;
+            T.flag = nullptr;
             T.part = nullptr;
-            T.parity = 0;
+            T.one_xcd = 0;
             if (threadIdx.x == 0) sh.idx = atomicAdd(A.counter, 1);
             __syncthreads();
             idx = __builtin_amdgcn_readfirstlane(sh.idx);
@@ -474,7 +570,7 @@ __global__ __launch_bounds__(512) void batched_kernel(Args A) {
             slot = A.slots2 + (int64_t)blockIdx.x * A.slot2_doubles;
         }
         solve_instance(A, A.inst[idx], slot, T, sh);
-        if (phase == 1) {
+        if (level < 2) {
             if (threadIdx.x == 0) sh.flag = atomicAdd(A.error, 0);
             __syncthreads();
             if (sh.flag != 0) break;
@@ -482,11 +578,13 @@ __global__ __launch_bounds__(512) void batched_kernel(Args A) {
     }
 }
 
-__global__ void reset_queue(int *counter, int start, int *large_counter, int *team_ctl, int nctl, int *error) {
-    for (int i = threadIdx.x; i < nctl; i += blockDim.x) team_ctl[i] = 0;
+__global__ void reset_queue(int *counter, int start, int *large, int *mid, int mid_start, int *flags, int nflags,
+                            int *error) {
+    for (int i = threadIdx.x; i < nflags; i += blockDim.x) flags[i] = 0;
     if (threadIdx.x == 0) {
         *counter = start;
-        *large_counter = 0;
+        *large = 0;
+        *mid = mid_start;
         *error = 0;
     }
 }
@@ -506,15 +604,6 @@ int device_cus() {
     return cus;
 }
 
-struct Layout {
-    size_t inst = 0, sample = 0, coef = 0, counter = 0, team_ctl = 0, team_part = 0, res = 0, occ = 0, slots = 0,
-           total = 0;
-    int64_t slot_doubles = 0, slot2_doubles = 0, coef_doubles = 0, occ_doubles = 0;
-    int grid = 0, m_max = 0, nslots = 0;
-    size_t slots2 = 0;
-    int teams = 0, n_large = 0;
-};
-
 constexpr int kSample = 32;
 
 // Work of one restart cycle of instance i (products plus Gram-Schmidt).
@@ -525,64 +614,90 @@ double instance_cost(int omega, int n, int krylov) {
     return dim * ((double)nn * (omega - nn) + 1.0 + 2.0 * m);
 }
 
-// Schedule: with a full grid (a multiple of 8 workgroups), 8 teams of grid/8
+// Schedule: with a full grid (a multiple of 64 workgroups), 8 teams of grid/8
 // workgroups (fewer and larger ones when fewer than 5 instances go to teams)
-// first solve the costliest instances (sorted order), then every workgroup
-// drains the rest alone.  Cost units are those of instance_cost
-// (work of one product).  A team runs an instance at 93% of its workgroups'
-// combined rate plus a fixed overhead per product (its cross-workgroup
-// barriers): kTeamOverhead, about 57 us against the ~4e9 units/s of one
-// workgroup, both measured on 4096 instances of the batched family.  Phase 1
-// takes sum (cost/(G * 0.93) + overhead) / teams, but no less than its
-// costliest instance on one team; phase 2 the larger of
-// (cost of the rest) / grid and one remaining instance times 3 (iteration
-// counts of equal-size instances differ by that much).  The split with the
-// lowest predicted time is taken: small instances stay on single workgroups,
-// where the barriers would cost more than the work.
+// first solve the costliest instances (sorted order), then grid/kMidTeam teams of
+// kMidTeam the next ones, and then every workgroup drains the rest alone.  Cost
+// units are those of instance_cost (work of one product).  A team runs an
+// instance at 93% of its workgroups' combined rate plus a fixed overhead per
+// product (its exchanges), about 23 us for 32 workgroups and 13 us for 8 against
+// the ~4.3e9 units/s of one, all measured.  A level takes the sum of its
+// instances over its teams, and its costliest instance once more for
+// teams that end at different times.  The split with the lowest predicted time is
+// taken: small instances stay on single workgroups, where the exchanges would
+// cost more than the work.  Measured, products of 64 instances at once: 3432
+// states 22-25 us on teams of 8, 72-75 us alone; 12870 states 53-59 us on teams of 8,
+// 38-41 us on teams of 32 of which there are a quarter as many (14.7 against 32.8 ms);
+// 184756 states 735-880 against 201-209 us (304 against 223 ms).  128 instances of
+// 45 to 184,756 states: 81 ms without the teams of 8, 67 ms with them.
 constexpr double kTeamEff = 0.93;
-constexpr double kTeamOverhead = 2.3e5;
-void plan_schedule(int count, const int *omega, const int *n, int krylov, int grid, const std::vector<int> &order,
-                   int *teams, int *n_large) {
-    *teams = 0;
-    *n_large = 0;
-    if (grid < 64 || grid % 8 != 0) return;
-    const int nteams = 8, G = grid / nteams;
-    std::vector<double> cost(count);
-    double total = 0.0;
-    for (int i = 0; i < count; ++i) total += (cost[i] = instance_cost(omega[i], n[i], krylov));
-    std::vector<double> t(count + 1);
-    double best = 1e300, done = 0.0, phase1 = 0.0;
-    for (int split = 0; split <= count; ++split) {
-        const double rest = total - done;
-        const double largest_rest = split < count ? cost[order[split]] : 0.0;
-        // Phase 1 cannot end before its costliest instance (order[0]) does on
-        // one team, however few instances share the teams.
-        const double p1 = split > 0 ? std::max(phase1 / nteams, cost[order[0]] / (G * kTeamEff) + kTeamOverhead)
-                                    : 0.0;
-        t[split] = p1 + std::max(rest / grid, 3.0 * largest_rest);
-        best = std::min(best, t[split]);
-        if (split < count) {
-            done += cost[order[split]];
-            phase1 += cost[order[split]] / (G * kTeamEff) + kTeamOverhead;
-        }
+constexpr double kTeamOverhead = 1.0e5, kMidOverhead = 5.5e4;
+constexpr int kMidTeam = 8;
+// The teams of 8 hold grid / 8 slots: up to this size (1.5 GB of them at krylov 20)
+// their vectors stay in the Infinity Cache's reach and the workspace small.
+constexpr int64_t kMidMaxDim = int64_t(1) << 18;
+constexpr int kMaxCandidates = 256;
+struct Schedule {
+    int teams = 0, n_large = 0;      // the large teams and their instances [0, n_large)
+    int mid_teams = 0, n_mid = 0;    // teams of kMidTeam: [n_large, n_large + n_mid)
+};
+Schedule plan_schedule(int count, const int *omega, const int *n, int krylov, int grid, const std::vector<int> &order) {
+    Schedule S;
+    if (grid < 64 || grid % 64 != 0) return S;
+    const int nteams = 8, G = grid / nteams, nmid = grid / kMidTeam;
+    std::vector<double> sum(count + 1, 0.0), cost(count + 1, 0.0);
+    for (int i = 0; i < count; ++i) {
+        cost[i] = instance_cost(omega[order[i]], n[order[i]], krylov);
+        sum[i + 1] = sum[i] + cost[i];
     }
-    for (int split = 0; split <= count; ++split)
-        if (t[split] == best) {
-            *n_large = split;
-            break;
+    const double rate = G * kTeamEff, mid_rate = kMidTeam * kTeamEff;
+    std::vector<int64_t> dim(count + 1, 0);   // the largest of the instances from i on
+    for (int i = count - 1; i >= 0; --i)
+        dim[i] = std::max<int64_t>(dim[i + 1], (int64_t)binom_host(omega[order[i]], n[order[i]]));
+    // candidates for the two splits: every count up to kMaxCandidates, evenly spread ones beyond
+    const int step = (count + kMaxCandidates - 1) / kMaxCandidates;
+    double best = 1e300;
+    for (int a = 0;; a = std::min(a + step, count)) {
+        const double t1 = a == 0 ? 0.0
+                                 : (sum[a] / rate + a * kTeamOverhead) / nteams + cost[0] / rate + kTeamOverhead;
+        for (int b = a;; b = std::min(b + step, count)) {
+            if (b > a && dim[a] > kMidMaxDim) break;
+            const double t2 = b == a ? 0.0
+                                     : ((sum[b] - sum[a]) / mid_rate + (b - a) * kMidOverhead) / nmid +
+                                           cost[a] / mid_rate + kMidOverhead;
+            const double t = t1 + t2 + (sum[count] - sum[b]) / grid + cost[b];
+            if (t < best) {
+                best = t;
+                S.n_large = a;
+                S.n_mid = b - a;
+            }
+            if (b == count) break;
         }
+        if (a == count) break;
+    }
     // Fewer large instances than teams: the fewest teams (a power of two, so
     // it divides the grid) that still start every large instance at once;
     // idle teams would only hold their slots.  Measured: one instance of
     // 8.6e7 states 26.0 s on one of 8 teams of 32 workgroups, 3.9 s on one
     // team of all 256 (and 122 -> 15 GB of workspace); two of 3.0e7 states
     // 10.4 -> 2.8 s on two teams of 128.
-    if (*n_large > 0) {
-        int t = 1;
-        while (t < *n_large && t < nteams) t <<= 1;
-        *teams = t;
+    if (S.n_large > 0) {
+        S.teams = 1;
+        while (S.teams < S.n_large && S.teams < nteams) S.teams <<= 1;
     }
+    if (S.n_mid > 0) S.mid_teams = nmid;
+    return S;
 }
+
+struct Layout {
+    size_t inst = 0, sample = 0, coef = 0, counter = 0, team_flag = 0, team_part = 0, res = 0, occ = 0, slots = 0,
+           total = 0;
+    int64_t slot_doubles = 0, mid_doubles = 0, slot2_doubles = 0, coef_doubles = 0, occ_doubles = 0;
+    int grid = 0, m_max = 0;
+    size_t slots_mid = 0, slots2 = 0;
+    Schedule plan;
+};
+
 
 std::vector<int> cost_order(int count, const int *omega, const int *n, int krylov) {
     std::vector<double> cost(count);
@@ -610,16 +725,17 @@ Layout layout_for(int count, const int *omega, const int *n, int krylov) {
     // fill every compute unit); one workgroup per instance otherwise.
     L.grid = device_cus();
     const std::vector<int> order = cost_order(count, omega, n, krylov);
-    plan_schedule(count, omega, n, krylov, L.grid, order, &L.teams, &L.n_large);
-    if (L.teams == 0) L.grid = std::min(count, L.grid);
-    // Team slots fit the largest instance; the single-workgroup slots fit the
-    // largest instance left after the team phase (sorted costliest first).
-    int64_t d2 = 0;
-    for (int q = L.n_large; q < count; ++q)
-        d2 = std::max<int64_t>(d2, (int64_t)binom_host(omega[order[q]], n[order[q]]));
-    L.slot_doubles = L.teams > 0 ? slot_for(dmax) : 0;
+    L.plan = plan_schedule(count, omega, n, krylov, L.grid, order);
+    const int n_large = L.plan.n_large, n_teams = n_large + L.plan.n_mid;
+    if (n_teams == 0) L.grid = std::min(count, L.grid);
+    // Slots fit the largest instance that they may hold (sorted costliest first).
+    auto dim_of = [&](int q) { return (int64_t)binom_host(omega[order[q]], n[order[q]]); };
+    int64_t d1 = 0, d2 = 0;
+    for (int q = n_large; q < n_teams; ++q) d1 = std::max(d1, dim_of(q));
+    for (int q = n_teams; q < count; ++q) d2 = std::max(d2, dim_of(q));
+    L.slot_doubles = n_large > 0 ? slot_for(dmax) : 0;
+    L.mid_doubles = d1 > 0 ? slot_for(d1) : 0;
     L.slot2_doubles = d2 > 0 ? slot_for(d2) : 0;
-    L.nslots = L.teams;
     size_t off = 0;
     L.inst = off;
     off += align256(sizeof(Instance) * (size_t)count);
@@ -627,18 +743,20 @@ Layout layout_for(int count, const int *omega, const int *n, int krylov) {
     off += align256(sizeof(Instance) * kSample);
     L.coef = off;
     off += align256(sizeof(double) * (size_t)L.coef_doubles);
-    L.counter = off;    // small queue at +0, large queue at +64, error flag at +128
+    L.counter = off;    // single-workgroup queue at +0, large teams' at +64, error flag at +128, the others' at +192
     off += 256;
-    L.team_ctl = off;
-    off += align256(sizeof(int) * kCtlInts * 8);
+    L.team_flag = off;
+    off += align256(sizeof(int) * 2 * (size_t)std::max(L.grid, 1));   // flags of both levels
     L.team_part = off;
-    off += align256(sizeof(double) * 16 * (size_t)std::max(L.grid, 1));
+    off += align256(sizeof(double) * 4 * kMaxSums * (size_t)std::max(L.grid, 1));   // sums of both levels
     L.res = off;
     off += align256(sizeof(Result) * (size_t)count);
     L.occ = off;
     off += align256(sizeof(double) * (size_t)L.occ_doubles);
     L.slots = off;
-    off += align256(sizeof(double) * (size_t)L.slot_doubles * (size_t)L.nslots);
+    off += align256(sizeof(double) * (size_t)L.slot_doubles * (size_t)L.plan.teams);
+    L.slots_mid = off;
+    off += align256(sizeof(double) * (size_t)L.mid_doubles * (size_t)L.plan.mid_teams);
     L.slots2 = off;
     off += sizeof(double) * (size_t)L.slot2_doubles * (size_t)L.grid;
     L.total = off;
@@ -739,7 +857,8 @@ pd_status batched_run(int count, const int *omega, const int *n, const double *e
     int *d_counter = reinterpret_cast<int *>(base + L.counter);
     int *d_large = reinterpret_cast<int *>(base + L.counter + 64);
     int *d_error = reinterpret_cast<int *>(base + L.counter + 128);
-    int *d_team_ctl = reinterpret_cast<int *>(base + L.team_ctl);
+    int *d_mid = reinterpret_cast<int *>(base + L.counter + 192);
+    int *d_team_flag = reinterpret_cast<int *>(base + L.team_flag);
     double *d_team_part = reinterpret_cast<double *>(base + L.team_part);
     Result *d_res = reinterpret_cast<Result *>(base + L.res);
     double *d_occ = reinterpret_cast<double *>(base + L.occ);
@@ -748,22 +867,31 @@ pd_status batched_run(int count, const int *omega, const int *n, const double *e
     PD_HIP(hipMemcpyAsync(d_coef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice, stream));
     PD_HIP(hipStreamSynchronize(stream));
 
-    const int teams = L.teams, n_large = L.n_large;
+    const Schedule &plan = L.plan;
     Args A;
     A.inst = d_inst;
     A.count = count;
-    A.n_large = n_large;
-    A.teams = teams;
-    A.team_size = teams ? L.grid / teams : 1;
     A.counter = d_counter;
-    A.large_counter = d_large;
-    A.team_ctl = d_team_ctl;
-    A.team_part = d_team_part;
+    Args::Level &large = A.level[0], &mid = A.level[1];
+    large.teams = plan.teams;
+    large.team_size = plan.teams ? L.grid / plan.teams : 1;
+    large.end = plan.n_large;
+    large.counter = d_large;
+    large.flag = d_team_flag;
+    large.part = d_team_part;
+    large.slots = d_slots;
+    large.slot_doubles = L.slot_doubles;
+    mid.teams = plan.mid_teams;
+    mid.team_size = kMidTeam;
+    mid.end = plan.n_large + plan.n_mid;
+    mid.counter = d_mid;
+    mid.flag = d_team_flag + L.grid;
+    mid.part = d_team_part + (size_t)2 * kMaxSums * L.grid;
+    mid.slots = reinterpret_cast<double *>(base + L.slots_mid);
+    mid.slot_doubles = L.mid_doubles;
     A.error = d_error;
     A.spin_limit = 1ll << 25;
     A.coef = d_coef;
-    A.slots = d_slots;
-    A.slot_doubles = L.slot_doubles;
     A.slots2 = reinterpret_cast<double *>(base + L.slots2);
     A.slot2_doubles = L.slot2_doubles;
     A.tol = o->tol;
@@ -798,13 +926,13 @@ pd_status batched_run(int count, const int *omega, const int *n, const double *e
             Args As = A;
             As.inst = d_sample;
             As.count = S;
-            if (L.teams > 0) {
-                As.n_large = S;           // the sample runs on teams (short trials)
-            } else {
-                As.n_large = 0;           // one workgroup per instance
-                As.teams = 0;
-            }
-            const int trial_grid = As.teams ? L.grid : std::min(S, L.grid);
+            // The sample runs on the largest teams there are (short trials), whose
+            // slots hold every instance; without teams, on single workgroups.
+            const bool on_teams = plan.teams > 0 || plan.mid_teams > 0;
+            As.level[0].end = plan.teams > 0 ? S : 0;
+            As.level[1].end = on_teams ? S : 0;
+            if (plan.teams > 0) As.level[1].teams = 0;
+            const int trial_grid = on_teams ? L.grid : std::min(S, L.grid);
             double best = 1e300;
             const int cands[3] = {128, 256, 512};
             struct Events {
@@ -818,8 +946,8 @@ pd_status batched_run(int count, const int *omega, const int *n, const double *e
             PD_HIP(hipEventCreate(&ev.b));
             block = 0;
             for (int c : cands) {
-                hipLaunchKernelGGL(reset_queue, dim3(1), dim3(64), 0, stream, d_counter, As.n_large, d_large,
-                                   d_team_ctl, kCtlInts * 8, d_error);
+                hipLaunchKernelGGL(reset_queue, dim3(1), dim3(64), 0, stream, d_counter, As.level[1].end, d_large,
+                                   d_mid, 0, d_team_flag, 2 * L.grid, d_error);
                 PD_HIP(hipEventRecord(ev.a, stream));
                 hipLaunchKernelGGL(batched_kernel, dim3(trial_grid), dim3(c), batched_dyn_lds(c), stream, As);
                 PD_HIP(hipGetLastError());
@@ -853,8 +981,8 @@ pd_status batched_run(int count, const int *omega, const int *n, const double *e
     PD_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(reset_queue, dim3(1), dim3(64), 0, cap, d_counter, n_large, d_large, d_team_ctl,
-                           kCtlInts * 8, d_error);
+        hipLaunchKernelGGL(reset_queue, dim3(1), dim3(64), 0, cap, d_counter, mid.end, d_large, d_mid, plan.n_large,
+                           d_team_flag, 2 * L.grid, d_error);
         hipLaunchKernelGGL(batched_kernel, dim3(L.grid), dim3(block), batched_dyn_lds(block), cap, A);
         e = hipStreamEndCapture(cap, &graph);
     }
@@ -908,9 +1036,10 @@ pd_status batched_run(int count, const int *omega, const int *n, const double *e
         binfo->kernel_seconds = kernel_seconds;
         binfo->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         binfo->converged = nconv;
-        binfo->teams = teams;
-        binfo->team_size = A.team_size;
-        binfo->large = n_large;
+        const Args::Level &first = plan.teams > 0 || plan.mid_teams == 0 ? large : mid;
+        binfo->teams = first.teams;
+        binfo->team_size = first.teams > 0 ? first.team_size : 1;
+        binfo->large = plan.teams > 0 ? plan.n_large : plan.n_mid;
         binfo->total_iterations = total_it;
     }
     if (nconv < count) return fail(PD_ENOCONV, "%d of %d instances did not converge", count - nconv, count);
