@@ -57,8 +57,9 @@ constexpr size_t kCoefBytes = (sizeof(CoefBlock) + 255) & ~size_t(255);
 // A basis handle carries kSigmaSlots coefficient blocks for pd_sigma, so
 // products on several streams can use one handle at once: a call takes a
 // block that is idle, or last used on its own stream (stream order protects
-// it), and otherwise makes its stream wait for the block's last product.
-constexpr int kSigmaSlots = 4;
+// it), and otherwise makes its stream wait for the block's last product.  The
+// first of them has no event while its stream is alone.
+constexpr int kSigmaSlots = 5;
 constexpr size_t kHandleBlockBytes = kSigmaSlots * kCoefBytes;
 
 inline size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -110,7 +111,8 @@ struct SigmaSlot {
     int has_coef = 0;
     int used = 0;                   // a product has been issued on it
     hipStream_t last_stream = nullptr;
-    hipEvent_t done = nullptr;      // recorded after its last product
+    hipEvent_t done = nullptr;      // recorded after its last product, if has_event
+    int has_event = 0;
 };
 
 // ---------------------------------------------------------------- windowed product

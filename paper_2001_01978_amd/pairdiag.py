@@ -154,9 +154,15 @@ def _check(status: int, allow=()):
     return status
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream(stream):
@@ -164,6 +170,18 @@ def _stream(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream)
+
+
+def _raw_stream(stream) -> int:
+    """The stream's handle as a number (of the current stream: without building
+    a torch.cuda.Stream object, which takes 3 us)."""
+    if stream is not None:
+        return stream.cuda_stream
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _dptr(t) -> ctypes.c_void_p:
@@ -359,7 +377,8 @@ class Basis:
             raise ValueError("x must be a contiguous vector of length dim")
         if y is None:
             y = torch.empty_like(x)
-        _check(load().pd_sigma(self._h, _hp(eps), _hp(V), dt, _dptr(x), _dptr(y), _stream(stream)))
+        _check(load().pd_sigma(self._h, eps.ctypes.data, V.ctypes.data, dt, x.data_ptr(), y.data_ptr(),
+                               _raw_stream(stream)))
         return y
 
     def warm_start(self, logits, x0=None, stream=None):
