@@ -162,15 +162,15 @@ struct WinPlan {
     WinPass pass[kMaxWinPasses];
     int npass;
 };
-// Spaces whose products go by windows: at least kMinWinDim states and kMinWinPairs
-// pairs (or holes).  A lane does the work of up to C(W, K) rows, so a small space
-// leaves the chip idle, and with few pairs most lanes own one or two window
-// states.  Measured, row kernel against windows, us in FP64 / FP32: Omega = 23, n = 8
-// (490,314 states) 62 / 48 against 62 / 57; Omega = 22, n = 11 (705,432) 79 / 67
-// against 59 / 47; Omega = 40, n = 6 (3.8e6) 571 / 366 against 717 / 449, n = 7
-// (1.9e7) 2524 / 1465 against 2122 / 1231.
-constexpr uint64_t kMinWinDim = 600000;
-constexpr int kMinWinPairs = 7;
+// Spaces whose products go by windows: kMinWinDim states with 8 pairs (or
+// holes) and more, kMinWinDim7 with 7.  A lane does the work of up to C(W, K) rows, so
+// a small space leaves the chip idle, and with few pairs most lanes own one
+// or two window states.  Measured, windows against a row per lane, us in FP64 / FP32:
+// Omega = 22, n = 11 (705,432 states) 56 / 44 against 46 / 31; Omega = 23, n = 11
+// (1.35e6) 71 / 61 against 90 / 64; Omega = 27, n = 8 (2.2e6) 144 / 94 against 168 / 105;
+// with 7 pairs Omega = 30 (2.0e6) 255 / 158 against 174 / 109, Omega = 33 (4.3e6)
+// 402 / 237 against 414 / 253; with 6, Omega = 40 (3.8e6) 717 / 449 against 476 / 281.
+constexpr uint64_t kMinWinDim = 1200000, kMinWinDim7 = 4200000;
 // Bytes of a space's plan on the device, 0 when its products take a row per lane.
 size_t window_plan_bytes(int omega, int n);
 // The plan with device pointers into dev, and in host the window_plan_bytes

@@ -435,6 +435,43 @@ __global__ __launch_bounds__(BLOCK, (sigma_min_waves<R, COMP, NN>())) void sigma
     }
 }
 
+// Spaces of less than kSmallDim states, 32-bit ranks: one tile of 256 rows per
+// workgroup and no tile counters, so that the tables of the next workgroups are
+// staged while others gather, and the register file holds what the compiler
+// wants.  Measured against the persistent kernel above, us in FP64 / FP32:
+// 12,870 states (16 orbits, 8 pairs) 9.2 / 8.4 -> 7.4 / 7.5 (the host's issue
+// rate), 352,716 (21, 10) 43.5 / 33.6 -> 25.2 / 17.6, 3.8e6 (40, 6) 568 / 364 -> 476 /
+// 281, but 6.5e6 (62, 5) 1394 / 1078 -> 1514 / 888: its tiles then run out of the
+// window of ranks that the counters keep together.  Two, four or eight lanes to
+// a row are no faster at any size (352,716 states: 30 / 52 / 72 us).
+constexpr int64_t kSmallDim = int64_t(1) << 22;
+constexpr int kSmallBlock = 256;
+constexpr int kSmallPairs = 12;   // C(25, 13) > kSmallDim
+template <typename R, typename T, int NN, bool COMP, bool BUF>
+__global__ __launch_bounds__(kSmallBlock) void sigma_small_kernel(Params<R, T> P) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int omega = P.omega, ks = P.ks;
+    R *Ct;
+    T *Vs, *ds;
+    stage_tables<R, T>(smem, omega, ks, P.V, P.d, Ct, Vs, ds, BUF ? (R)sizeof(T) : (R)1);
+    R *pre = reinterpret_cast<R *>(smem + ((table_bytes<R, T>(omega, ks) + 15) & ~size_t(15)));
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t xr = x_resource<T>(P.x, P.dim);   // used by the BUF gathers only
+    const int64_t row = (int64_t)blockIdx.x * kSmallBlock + threadIdx.x;
+    if (row >= P.dim) return;
+    if (omega <= 32)
+        P.y[row] = sigma_row<R, T, NN, COMP, BUF, 0, true, true>(row, P.dim, omega, ks, Ct, Vs, ds, P.dsum, P.x, pre,
+                                                                 kSmallBlock, xr);
+    else
+        P.y[row] = sigma_row<R, T, NN, COMP, BUF, 0, true>(row, P.dim, omega, ks, Ct, Vs, ds, P.dsum, P.x, pre,
+                                                           kSmallBlock, xr);
+}
+
+template <typename R, typename T, int NN>
+constexpr bool sigma_small_pairs() {
+    return sizeof(R) == 4 && NN <= kSmallPairs;
+}
+
 // Dynamic LDS limit to set on an instantiation with NN pairs and BLOCK
 // threads: the most any omega <= 62 can ask of it (tables plus per-lane
 // slots), capped at what a CU holds.  One value per instantiation, so calls
@@ -494,6 +531,17 @@ LaunchShape choose_shape(int omega, int ks) {
 
 template <typename R, typename T, int NN, bool COMP>
 hipError_t launch_nn(const Params<R, T> &P, hipStream_t stream) {
+    if constexpr (sigma_small_pairs<R, T, NN>()) {
+        if (P.dim < kSmallDim) {
+            constexpr bool kBuf = sizeof(T) == 4;
+            const size_t smem = ((table_bytes<R, T>(P.omega, P.ks) + 15) & ~size_t(15)) + prefix_bytes<R>(NN, kSmallBlock);
+            const int64_t grid = (P.dim + kSmallBlock - 1) / kSmallBlock;
+            if (smem > 64 * 1024) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((sigma_small_kernel<R, T, NN, COMP, kBuf>), dim3((unsigned)grid), dim3(kSmallBlock), smem,
+                               stream, P);
+            return hipGetLastError();
+        }
+    }
     const LaunchShape sh = choose_shape<R, T, NN>(P.omega, P.ks);
     // Byte-offset buffer gathers (FP32, every byte offset of x within 32 bits;
     // measured slower than 64-bit global loads for FP64 gathers).

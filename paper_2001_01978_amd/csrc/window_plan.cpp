@@ -136,9 +136,10 @@ bool segment_classes(int omega, int n, SegPlan &p) {
 }
 
 bool all_passes(int omega, int n, Passes &ps) {
-    if (omega > kMaxWinOmega || std::min(n, omega - n) < kMinWinPairs) return false;
+    const int pairs = std::min(n, omega - n);
+    if (omega > kMaxWinOmega || pairs < 7) return false;
     const uint64_t dim = binom_host(omega, n);
-    if (dim < kMinWinDim) return false;
+    if (dim < (pairs == 7 ? kMinWinDim7 : kMinWinDim)) return false;
     int W[kMaxWinPasses];
     const int np = cut_orbits(omega, dim, W);
     if (np == 0) return false;

@@ -1,9 +1,10 @@
-"""GPU: products of large full spaces, which go by orbit windows (window_impl.h).
+"""GPU: products of large full spaces, which go by orbit windows (window_impl.h),
+and of the spaces below them, which take a row per lane (sigma_small_kernel).
 
-The spaces cover every window width (4 to 8 orbits), one, two and three
-windows, half-filled, sparse and mirrored fillings, and both sides of the
-rules that choose the product's kernels.  Inputs are dyadic (every product and
-partial sum exact), so results are compared with the oracle bit for bit.
+The spaces cover every window width, one, two and three windows, half-filled,
+sparse and mirrored fillings, and both sides of the rules that choose the
+product's kernels.  Inputs are dyadic (every product and partial sum exact),
+so results are compared with the oracle bit for bit.
 """
 import math
 
@@ -15,16 +16,19 @@ from paper_2001_01978_amd import inputs
 pytestmark = pytest.mark.gpu
 
 SPACES = [
-    (22, 11),            # the smallest: one window of 6
-    (23, 8),             # just below the smallest space: a row per lane
-    (23, 9), (23, 14),   # one window of 7
-    (24, 8), (24, 12),   # two windows of 4; one of 8
-    (24, 6),             # below the smallest number of pairs
+    (17, 1), (17, 16),   # a row per lane: one tile and a remainder
+    (21, 10), (20, 14),  # a row per lane
+    (40, 4), (36, 33),   # the same with 64-bit state words
+    (23, 10),            # just below the smallest space of windows
+    (23, 11), (23, 12),  # one window of 7
+    (24, 10), (24, 14),  # two windows of 4
+    (24, 12),            # one window of 8
     (25, 9), (25, 16),   # windows of 5 and 4
-    (26, 7), (26, 19),   # two windows of 5, the fewest pairs
-    (27, 19),            # windows of 6 and 5
-    (29, 7),             # windows of 7 and 6
-    (31, 24),            # windows of 8 and 7
+    (26, 9), (26, 17),   # two windows of 5
+    (27, 8), (27, 19),   # windows of 6 and 5, the fewest pairs
+    (28, 8),             # two windows of 6
+    (29, 8),             # windows of 7 and 6
+    (31, 8), (31, 24),   # windows of 8 and 7; 7 pairs: a row per lane
     (33, 7),             # three windows (6, 6, 5), short segments in groups
 ]
 
