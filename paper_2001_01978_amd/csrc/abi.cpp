@@ -196,7 +196,7 @@ DiagBins make_bins(int omega, const double *d, double dmin, double dmax, int64_t
 }
 
 struct TruncLayout {
-    size_t words, kranks, scan, total;
+    size_t words, supers, kranks, scan, total;
     int64_t W;
 };
 TruncLayout trunc_layout(int64_t full_dim, int64_t kept) {
@@ -205,6 +205,8 @@ TruncLayout trunc_layout(int64_t full_dim, int64_t kept) {
     size_t off = kHandleBlockBytes;
     L.words = off;
     off += align256((size_t)L.W * sizeof(TruncWord));
+    L.supers = off;
+    if (trunc_ranks32(full_dim)) off += align256((size_t)trunc_supers(full_dim) * sizeof(uint32_t));
     L.kranks = off;
     off += align256((size_t)kept * (trunc_ranks32(full_dim) ? 4 : 8));
     L.scan = off;
@@ -654,6 +656,9 @@ pd_status pd_basis_create_truncated(int omega, int n, const double *eps, const d
     TruncWord last;
     hipError_t e = launch_trunc_build(omega, n, full_dim, db, info->cut_bin, words, scan, kranks, info->kept, stream);
     if (e == hipSuccess) e = hipMemcpyAsync(&last, words + (L.W - 1), sizeof(last), hipMemcpyDeviceToHost, stream);
+    const bool cells = trunc_ranks32(full_dim);
+    uint32_t *supers = reinterpret_cast<uint32_t *>(base + L.supers);
+    if (e == hipSuccess && cells) e = launch_trunc_cells(full_dim, words, supers, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return fail(PD_EDEVICE, "truncated basis: %s", hipGetErrorString(e));
     const int64_t built = (int64_t)(last.base + (uint64_t)__builtin_popcountll(last.bits));
@@ -669,7 +674,9 @@ pd_status pd_basis_create_truncated(int omega, int n, const double *eps, const d
     b->trunc.full_dim = full_dim;
     b->trunc.kept = info->kept;
     b->trunc.kranks = kranks;
-    b->trunc.words = words;
+    b->trunc.words = cells ? nullptr : words;
+    b->trunc.cells = cells ? reinterpret_cast<const uint32_t *>(words) : nullptr;
+    b->trunc.supers = cells ? supers : nullptr;
     b->trunc.index_mode = index_mode == PD_TRUNC_BSEARCH ? kTruncBsearch : kTruncBitmap;
     *out = b;
     return PD_OK;

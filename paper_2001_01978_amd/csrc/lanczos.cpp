@@ -222,12 +222,26 @@ pd_status lanczos_run(pd_basis b, const CoefBlock &host_coef, const pd_lanczos_o
                 if ((st >> q) & 1ull) r += (int64_t)binom_host(q, ++j);
             if (tr) {
                 // Its row in the truncated space (the lowest diagonal is always kept).
-                TruncWord wd;
-                PD_HIP(hipMemcpyAsync(&wd, tr->words + (r >> 6), sizeof(wd), hipMemcpyDeviceToHost, s));
-                PD_HIP(hipStreamSynchronize(s));
-                const int sh = (int)(r & 63);
-                if (!((wd.bits >> sh) & 1ull)) return fail(PD_EINVAL, "the HF state is not in the truncated space");
-                r = (int64_t)wd.base + __builtin_popcountll(wd.bits & ((1ull << sh) - 1));
+                uint64_t bits = 0, row = 0;
+                int sh = 0;
+                if (tr->cells) {
+                    uint32_t cell = 0, super = 0;
+                    PD_HIP(hipMemcpyAsync(&cell, tr->cells + (r >> kCellBits), 4, hipMemcpyDeviceToHost, s));
+                    PD_HIP(hipMemcpyAsync(&super, tr->supers + (r >> kSuperBits), 4, hipMemcpyDeviceToHost, s));
+                    PD_HIP(hipStreamSynchronize(s));
+                    bits = cell & 0xFFFFu;
+                    row = (uint64_t)super + (cell >> 16);
+                    sh = (int)(r & 15);
+                } else {
+                    TruncWord wd;
+                    PD_HIP(hipMemcpyAsync(&wd, tr->words + (r >> 6), sizeof(wd), hipMemcpyDeviceToHost, s));
+                    PD_HIP(hipStreamSynchronize(s));
+                    bits = wd.bits;
+                    row = wd.base;
+                    sh = (int)(r & 63);
+                }
+                if (!((bits >> sh) & 1ull)) return fail(PD_EINVAL, "the HF state is not in the truncated space");
+                r = (int64_t)row + __builtin_popcountll(bits & ((1ull << sh) - 1));
             }
             PD_HIP(launch_fill_unit(dim, r, w, s));
             break;

@@ -85,20 +85,28 @@ pd_status pack_coefficients(int omega, int n, const double *eps, const double *V
 // ---------------------------------------------------------------- truncated spaces
 // Sec. 3.5: a subset of the full (omega, n) space, kept in ascending order.
 // Row i of a truncated vector is the state of full rank kranks[i].  The
-// rank -> index map is one word per 64 full ranks: which of them are kept,
-// and how many kept ranks precede the word.
+// rank -> index map is built as one word per 64 full ranks: which of them are
+// kept, and how many kept ranks precede the word.  With 32-bit ranks (full_dim <
+// 2^32) the product reads it as cells of half the width, put in the words'
+// place: 16 ranks in 32 bits, the kept ones in the lower half and in the upper
+// half how many kept ranks lie between the cell and the start of its block of
+// 2^16 ranks; supers[] holds the kept ranks before each block.
 struct alignas(16) TruncWord {
     uint64_t bits;
     uint64_t base;
 };
+constexpr int kCellBits = 4, kSuperBits = 16;   // ranks of a cell, of a block (powers of 2)
 enum { kTruncBitmap = 0, kTruncBsearch = 1 };
 struct TruncSpace {
     int64_t full_dim;
     int64_t kept;
     const void *kranks;       // uint32 when full_dim < 2^32, else uint64
-    const TruncWord *words;   // ceil(full_dim / 64)
+    const TruncWord *words;   // ceil(full_dim / 64), 64-bit ranks only
+    const uint32_t *cells;    // 4 per word, 32-bit ranks only
+    const uint32_t *supers;   // ceil(full_dim / 2^16), 32-bit ranks only
     int index_mode;           // kTruncBitmap or kTruncBsearch (target index by binary search over kranks)
 };
+inline int64_t trunc_supers(int64_t full_dim) { return (full_dim + (1 << kSuperBits) - 1) >> kSuperBits; }
 inline bool trunc_ranks32(int64_t full_dim) { return full_dim < (int64_t(1) << 32); }
 
 }  // namespace pd
@@ -311,6 +319,8 @@ constexpr int64_t kMaxTruncBins = int64_t(1) << 30;
 hipError_t launch_trunc_ranks64(const TruncSpace &tr, int64_t *out, hipStream_t s);
 hipError_t launch_trunc_build(int omega, int n, int64_t full_dim, const DiagBins &db, int64_t cut_bin,
                               TruncWord *words, uint64_t *scan_tmp, void *kranks, int64_t cap, hipStream_t s);
+// Rewrites the words of a 32-bit space as cells, in place, and fills supers.
+hipError_t launch_trunc_cells(int64_t full_dim, TruncWord *words, uint32_t *supers, hipStream_t s);
 
 // batched.hip
 size_t batched_workspace_bytes(int count, const int *omega, const int *n, const pd_lanczos_opts *o);

@@ -122,11 +122,22 @@ __device__ __forceinline__ T buffer_gather(__amdgpu_buffer_rsrc_t rs, uint32_t b
 //   MAP 1: one 16-byte word per 64 full ranks (kept bits, kept count before
 //          the word): row = base + popcount(bits below the rank);
 //   MAP 2: binary search over the ascending kept ranks (the paper's search
-//          for truncated spaces), all NN searches of a hop block in lockstep.
+//          for truncated spaces), all NN searches of a hop block in lockstep;
+//   MAP 3, 4 (32-bit ranks): one 4-byte cell per 16 full ranks (kept bits,
+//          kept count since the start of its block of 2^16 ranks) and the blocks'
+//          counts, which MAP 3 has in LDS: row = block + cell + popcount(bits below).
+// A hop is bound by the texture addresser: 8 cycles for a wave's cells and 16 to 20
+// for its elements where MAP 1's words take another 16, and 10 instead of 25 VALU
+// instructions.  The elements of dropped targets are loaded too (a neighbour's)
+// and replaced by 0 afterwards: a branch around each load kept them from being
+// in flight together.  1e7 of 4.0e7 states (28 orbits), FP64: 2289 us with MAP 1,
+// 1848 with cells, 1546 without the branches.
 template <typename R>
 struct TruncMap {
     const R *kranks = nullptr;
     const TruncWord *words = nullptr;
+    const uint32_t *cells = nullptr;
+    const uint32_t *supers = nullptr;   // in LDS for MAP 3
     int64_t kept = 0;
     int64_t self = 0;   // this row's index in the truncated space
 };
@@ -145,6 +156,24 @@ __device__ __forceinline__ void map_gather(const TruncMap<R> &tm, const T *__res
             const bool kept = (w[r].bits >> sh) & 1ull;
             xv[r] = kept ? x[(int64_t)w[r].base + __popcll(below)] : T(0);
         }
+    } else if constexpr (MAP >= 3) {
+        uint32_t w[NN > 0 ? NN : 1];
+        const uint32_t last = (uint32_t)tm.kept - 1;
+#pragma unroll
+        for (int r = 0; r < NN; ++r) w[r] = tm.cells[jt[r] >> kCellBits];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < NN; ++r) {
+            const uint32_t sh = jt[r] & 15u;
+            uint32_t row = tm.supers[jt[r] >> kSuperBits] + (w[r] >> 16) +
+                           (uint32_t)__popc(__builtin_amdgcn_ubfe(w[r], 0, sh));
+            // of a target left out: the next kept row's element, not used
+            row = row < last ? row : last;
+            xv[r] = x[row];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < NN; ++r) xv[r] = (w[r] >> (jt[r] & 15u)) & 1u ? xv[r] : T(0);
     } else {
         int64_t lo[NN > 0 ? NN : 1];
 #pragma unroll
@@ -590,8 +619,13 @@ struct TruncParams {
     Params<R, T> P;       // P.dim = full dimension, P.ntiles over the kept rows
     const R *kranks;
     const TruncWord *words;
+    const uint32_t *cells, *supers;
+    int nsupers;
     int64_t kept;
 };
+
+// Blocks' counts that a workgroup keeps in LDS (8 KB: spaces up to 1.3e8 states).
+constexpr int kLdsSupers = 2048;
 
 template <typename R, typename T, int NN, bool COMP, int BLOCK, int MAP>
 __global__ __launch_bounds__(BLOCK) void sigma_trunc_kernel(TruncParams<R, T> Q) {
@@ -602,12 +636,19 @@ __global__ __launch_bounds__(BLOCK) void sigma_trunc_kernel(TruncParams<R, T> Q)
     T *Vs, *ds;
     stage_tables<R, T>(smem, omega, ks, P.V, P.d, Ct, Vs, ds);
     R *pre = reinterpret_cast<R *>(smem + ((table_bytes<R, T>(omega, ks) + 15) & ~size_t(15)));
-    __syncthreads();
-    const __amdgpu_buffer_rsrc_t xr = x_resource<T>(P.x, 1);   // unused (MAP gathers)
     TruncMap<R> tm;
     tm.kranks = Q.kranks;
     tm.words = Q.words;
+    tm.cells = Q.cells;
+    tm.supers = Q.supers;
     tm.kept = Q.kept;
+    if constexpr (MAP == 3) {
+        __shared__ uint32_t sup[kLdsSupers];
+        for (int i = threadIdx.x; i < Q.nsupers; i += BLOCK) sup[i] = Q.supers[i];
+        tm.supers = sup;
+    }
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t xr = x_resource<T>(P.x, 1);   // unused (MAP gathers)
     for (int64_t tile = blockIdx.x; tile < P.ntiles; tile += gridDim.x) {
         const int64_t i = tile * BLOCK + threadIdx.x;
         if (i >= Q.kept) continue;
@@ -617,25 +658,31 @@ __global__ __launch_bounds__(BLOCK) void sigma_trunc_kernel(TruncParams<R, T> Q)
     }
 }
 
-template <typename R, typename T, int NN, bool COMP>
-hipError_t launch_trunc_nn(TruncParams<R, T> Q, int mode, hipStream_t stream) {
+template <typename R, typename T, int NN, bool COMP, int MAP>
+hipError_t launch_trunc_map(TruncParams<R, T> Q, hipStream_t stream) {
     constexpr int B = 256;
     const size_t smem = ((table_bytes<R, T>(Q.P.omega, Q.P.ks) + 15) & ~size_t(15)) + prefix_bytes<R>(NN, B);
-    const void *fn = mode == kTruncBsearch ? reinterpret_cast<const void *>(&sigma_trunc_kernel<R, T, NN, COMP, B, 2>)
-                                           : reinterpret_cast<const void *>(&sigma_trunc_kernel<R, T, NN, COMP, B, 1>);
-    if (smem > 64 * 1024) {
+    if (smem + (MAP == 3 ? kLdsSupers * sizeof(uint32_t) : 0) > 64 * 1024) {
         constexpr size_t lim = lds_limit<R, T, NN, B>();
         if (smem > lim) return hipErrorInvalidValue;
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&sigma_trunc_kernel<R, T, NN, COMP, B, MAP>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim);
         if (e != hipSuccess) return e;
     }
     Q.P.ntiles = (Q.kept + B - 1) / B;
     const int64_t grid = Q.P.ntiles < kMaxGrid ? Q.P.ntiles : kMaxGrid;
-    if (mode == kTruncBsearch)
-        hipLaunchKernelGGL((sigma_trunc_kernel<R, T, NN, COMP, B, 2>), dim3((unsigned)grid), dim3(B), smem, stream, Q);
-    else
-        hipLaunchKernelGGL((sigma_trunc_kernel<R, T, NN, COMP, B, 1>), dim3((unsigned)grid), dim3(B), smem, stream, Q);
+    hipLaunchKernelGGL((sigma_trunc_kernel<R, T, NN, COMP, B, MAP>), dim3((unsigned)grid), dim3(B), smem, stream, Q);
     return hipGetLastError();
+}
+
+template <typename R, typename T, int NN, bool COMP>
+hipError_t launch_trunc_nn(const TruncParams<R, T> &Q, int mode, hipStream_t stream) {
+    if (mode == kTruncBsearch) return launch_trunc_map<R, T, NN, COMP, 2>(Q, stream);
+    if constexpr (sizeof(R) == 4)
+        return Q.nsupers <= kLdsSupers ? launch_trunc_map<R, T, NN, COMP, 3>(Q, stream)
+                                       : launch_trunc_map<R, T, NN, COMP, 4>(Q, stream);
+    else
+        return launch_trunc_map<R, T, NN, COMP, 1>(Q, stream);
 }
 
 template <typename R, typename T, bool COMP>
@@ -671,6 +718,9 @@ hipError_t launch_trunc_typed(int omega, int n, const TruncSpace &tr, const T *d
     Q.P.chunk = 0;
     Q.kranks = static_cast<const R *>(tr.kranks);
     Q.words = tr.words;
+    Q.cells = tr.cells;
+    Q.supers = tr.supers;
+    Q.nsupers = (int)std::min<int64_t>(trunc_supers(tr.full_dim), 1 << 30);
     Q.kept = tr.kept;
     return comp ? dispatch_trunc_nn<R, T, true>(Q, tr.index_mode, stream)
                 : dispatch_trunc_nn<R, T, false>(Q, tr.index_mode, stream);

@@ -253,6 +253,27 @@ __global__ __launch_bounds__(kT) void scan_add_kernel(TruncWord *words, int64_t 
 
 // kranks holds `cap` entries; a selection that keeps more (a caller's info
 // that does not match the cut) writes none past it and is rejected afterwards.
+__global__ __launch_bounds__(kT) void supers_kernel(const TruncWord *words, int64_t count, uint32_t *supers) {
+    for (int64_t b = blockIdx.x * (int64_t)kT + threadIdx.x; b < count; b += (int64_t)gridDim.x * kT)
+        supers[b] = (uint32_t)words[b << (kSuperBits - 6)].base;
+}
+
+// Each word becomes its four cells, read and written by one thread.
+__global__ __launch_bounds__(kT) void cells_kernel(TruncWord *words, int64_t W, const uint32_t *supers) {
+    for (int64_t w = blockIdx.x * (int64_t)kT + threadIdx.x; w < W; w += (int64_t)gridDim.x * kT) {
+        const TruncWord t = words[w];
+        uint32_t before = (uint32_t)t.base - supers[w >> (kSuperBits - 6)];
+        uint32_t cell[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t bits = (uint32_t)(t.bits >> (16 * i)) & 0xFFFFu;
+            cell[i] = bits | before << 16;
+            before += (uint32_t)__popc(bits);
+        }
+        *reinterpret_cast<uint4 *>(words + w) = make_uint4(cell[0], cell[1], cell[2], cell[3]);
+    }
+}
+
 template <typename R>
 __global__ __launch_bounds__(kT) void ranks_kernel(const TruncWord *words, int64_t W, R *kranks, uint64_t cap) {
     for (int64_t w = blockIdx.x * (int64_t)kT + threadIdx.x; w < W; w += (int64_t)gridDim.x * kT) {
@@ -293,6 +314,13 @@ hipError_t launch_trunc_cut(int omega, int n, int64_t full_dim, const DiagBins &
 size_t trunc_scan_words(int64_t full_dim) {
     const int64_t W = (full_dim + 63) / 64;
     return (size_t)((W + kScanPer - 1) / kScanPer);
+}
+
+hipError_t launch_trunc_cells(int64_t full_dim, TruncWord *words, uint32_t *supers, hipStream_t s) {
+    const int64_t W = (full_dim + 63) / 64, n = trunc_supers(full_dim);
+    hipLaunchKernelGGL(supers_kernel, dim3(blocks_for(n)), dim3(kT), 0, s, (const TruncWord *)words, n, supers);
+    hipLaunchKernelGGL(cells_kernel, dim3(blocks_for(W)), dim3(kT), 0, s, words, W, (const uint32_t *)supers);
+    return hipGetLastError();
 }
 
 hipError_t launch_trunc_build(int omega, int n, int64_t full_dim, const DiagBins &db, int64_t cut_bin,
