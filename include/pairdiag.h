@@ -230,8 +230,8 @@ typedef struct {
     double residual;     /* final rho */
     double monopole_min; /* smallest diagonal element (Monopole_Min, Sec. 4.3) */
     double seconds;      /* wall time of the call */
-    double sigma_seconds_f64;  /* summed device time of the FP64 products (HIP events) */
-    double sigma_seconds_f32;  /* summed device time of the FP32 products (HIP events) */
+    double sigma_seconds_f64;  /* summed device time of the FP64 products (device clock, launch gaps included) */
+    double sigma_seconds_f32;  /* summed device time of the FP32 products (same) */
     int fallback_used;         /* 1 if the fallback replaced the caller's start vector */
     int reorth_second_passes;  /* steps whose Gram-Schmidt needed the second pass */
 } pd_lanczos_info;

@@ -52,11 +52,12 @@ struct Layout {
     int m = 0;
 };
 
-constexpr int kScalars = 512;  // doubles: c[66], c2[65], nrm2, sum, occ[64]
-constexpr int kOffC = 0, kOffC2 = 80, kOffNrm = 192, kOffSum = 193, kOffOcc = 256;
-// Thresholds of the second Gram-Schmidt pass (see the step description above).
-constexpr double kReorthEta = 0.70710678118654752;   // 1/sqrt(2)
-constexpr double kReorthTau = 1.0 / 128.0;
+constexpr int kScalars = 512;  // doubles of LanczosScalars
+constexpr int off_of(size_t bytes) { return (int)(bytes / sizeof(double)); }
+constexpr int kOffC = 0, kOffNrm = off_of(offsetof(LanczosScalars, nrm)),
+              kOffSum = off_of(offsetof(LanczosScalars, sum)), kOffOcc = off_of(offsetof(LanczosScalars, occ)),
+              kOffAgain = off_of(offsetof(LanczosScalars, again)), kOffAlpha = off_of(offsetof(LanczosScalars, alpha)),
+              kOffBeta = off_of(offsetof(LanczosScalars, beta));
 // precision value 2: FP32 products, every Krylov column stored in FP64
 constexpr int kMixedF64Cols = 2;
 
@@ -97,20 +98,24 @@ Layout layout_for(int64_t dim, int krylov, int precision) {
     return L;
 }
 
+// The scales, recurrence terms and the choice of a second pass are computed on the
+// device (LanczosScalars), so the steps of a cycle are queued without a wait.
+// The host waits for step k of m only after the first step, which decides about the
+// cycle, after the last, and in between at doubling steps, so that an invariant
+// subspace of r vectors costs fewer than r products more (from it on v = 0, and
+// the zero scale keeps the queued steps finite).  A wait costs 30 us of an
+// idle chip: at 24 orbits (2.7e6 rows, 221 steps) a solve took 59.2 ms waiting
+// for each step and 52.2 so; at 28 orbits (4e7) 431 and 419.  From 2^26 rows
+// a step takes over 3 ms, the wait under 1% of it, and every step is waited for.
+constexpr int64_t kQueueDim = (int64_t)1 << 26;
+bool ends_wait(int k, int m, int64_t dim) { return (k & (k + 1)) == 0 || k + 1 == m || dim >= kQueueDim; }
+
 struct Dev {
     hipStream_t s;
     double *scal;
     double host[kScalars];
     hipError_t fetch(int off, int count) {
         hipError_t e = hipMemcpyAsync(host + off, scal + off, count * sizeof(double), hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) return e;
-        return hipStreamSynchronize(s);
-    }
-    // one synchronisation for two ranges
-    hipError_t fetch2(int off1, int count1, int off2, int count2) {
-        hipError_t e = hipMemcpyAsync(host + off1, scal + off1, count1 * sizeof(double), hipMemcpyDeviceToHost, s);
-        if (e != hipSuccess) return e;
-        e = hipMemcpyAsync(host + off2, scal + off2, count2 * sizeof(double), hipMemcpyDeviceToHost, s);
         if (e != hipSuccess) return e;
         return hipStreamSynchronize(s);
     }
@@ -289,40 +294,28 @@ pd_status lanczos_run(pd_basis b, const CoefBlock &host_coef, const pd_lanczos_o
         }
     }
 
-    // HIP events around every product: its device time, read after the step's sync
-    struct Events {
-        hipEvent_t a = nullptr, b = nullptr;
-        ~Events() {
-            if (a) (void)hipEventDestroy(a);
-            if (b) (void)hipEventDestroy(b);
-        }
-    } ev;
-    if (time_products) {
-        PD_HIP(hipEventCreate(&ev.a));
-        PD_HIP(hipEventCreate(&ev.b));
-    }
-
+    LanczosScalars *scalars = reinterpret_cast<LanczosScalars *>(scal);
     std::vector<double> alpha(m), beta(m), y(m), yy(m);
-    // Column scales: q_j = sc[j] * (stored column j).  Columns are written
-    // unnormalised by the Gram-Schmidt pass itself; 1/beta is kept here.
-    std::vector<double> sc(m + 1, 1.0);
-    // Part of the three-term recurrence subtracted before the projection:
-    // sigma_k q_k + beta_{k-1} q_{k-1}, with sigma_k = alpha_{k-1} (the Ritz
-    // value of the previous cycle at k = 0), as coefficients of stored columns.
-    std::vector<double> d(m, 0.0);
+    {
+        const double zero[4] = {0.0, 0.0, 0.0, 0.0}, one = 1.0;   // again, passes, ticks; sc[0]
+        PD_HIP(hipMemcpyAsync(&scalars->again, zero, sizeof(zero), hipMemcpyHostToDevice, s));
+        PD_HIP(hipMemcpyAsync(&scalars->sc[0], &one, sizeof(one), hipMemcpyHostToDevice, s));
+        PD_HIP(hipStreamSynchronize(s));
+    }
     double theta = 0.0, residual = INFINITY, e0 = NAN;
     bool converged = false;
     bool final_check = false;  // this cycle only measures its start vector
     int cycle = 0;
     for (cycle = 0;; ++cycle) {
         int m_eff = m;
-        sc[0] = 1.0;
+        int taken = 0;        // coefficients fetched so far
+        double tnorm = 0.0;
+        PD_HIP(launch_stamp(scalars, s));
         for (int k = 0; k < m; ++k) {
             double *qk = Q + (size_t)k * ld;
             const bool f32_step = y32 && k >= 1;
             // the product of the stored column k (FP32 column for FP32 steps); H q_k = sc[k] * it
             const void *pin = f32_step ? static_cast<const void *>(y32) : static_cast<const void *>(p);
-            if (time_products) PD_HIP(hipEventRecord(ev.a, s));
             if (f32_step) {
                 PD_HIP(launch_sigma(omega, n, dim, coef, PD_F32, Q32 ? Q32 + (size_t)(k - 1) * ld : x32, y32, s,
                                     dsum64, dsum32, tr, plan));
@@ -330,47 +323,36 @@ pd_status lanczos_run(pd_basis b, const CoefBlock &host_coef, const pd_lanczos_o
             } else {
                 PD_HIP(launch_sigma(omega, n, dim, coef, PD_F64, qk, p, s, dsum64, dsum32, tr, plan));
             }
-            if (time_products) PD_HIP(hipEventRecord(ev.b, s));
             ++info.iterations;
-            const double sp = sc[k];
-            const double sigma = k > 0 ? alpha[k - 1] : theta;
-            std::fill(d.begin(), d.begin() + k + 1, 0.0);
-            d[k] = sigma * sc[k];
-            if (k > 0) d[k - 1] = beta[k - 1] * sc[k - 1];
+            const LanczosStep step{scalars, k, theta, f32_step ? 1 : 0};
             // ps = H q_k - sigma q_k - beta_{k-1} q_{k-1}; c = Q^T ps (alpha_k = sigma + c_k),
             // ||ps||^2 and ||H q_k||^2
-            PD_HIP(launch_project(Q, ld, k + 1, dim, pin, f32_step, sp, sc.data(), d.data(), partials,
-                                  scal + kOffC, s, Q32));
+            PD_HIP(launch_project(Q, ld, k + 1, dim, pin, f32_step, 0.0, nullptr, nullptr, partials, nullptr, s, Q32,
+                                  &step));
             const bool store = k + 1 < m;      // q_{k+1} is needed (else only alpha_k, and beta_0 at k = 0)
-            double nrm_v = 0.0;
             if (store || k == 0) {
                 // v = H q_k - Q c, written as the next stored column (FP32 in mixed
-                // precision; or into w), with c' = Q^T v, ||v||^2
+                // precision; or into w), with c' = Q^T v, ||v||^2; then, after a
+                // large cancellation, Gram-Schmidt once more: v -= Q c'
                 double *dst = store ? (Q32 ? nullptr : Q + (size_t)(k + 1) * ld) : w;
                 float *dst32 = store ? (Q32 ? Q32 + (size_t)k * ld : x32) : nullptr;
-                PD_HIP(launch_update_project(Q, ld, k + 1, dim, scal + kOffC, sc.data(), d.data(), pin, f32_step,
-                                             sp, dst, dst32, partials, scal + kOffC2, s, Q32));
-                PD_HIP(dev.fetch2(kOffC + k, 3, kOffC2 + k + 1, 1));
-                nrm_v = dev.host[kOffC2 + k + 1];
-                const double nrm_ps = dev.host[kOffC + k + 1], nrm_hq = dev.host[kOffC + k + 2];
-                if (!(nrm_v >= kReorthEta * kReorthEta * nrm_ps && nrm_v >= kReorthTau * kReorthTau * nrm_hq)) {
-                    // large cancellation: Gram-Schmidt once more, v -= Q c'
-                    PD_HIP(launch_update_norm(Q, ld, k + 1, dim, scal + kOffC2, sc.data(), dst, dst32, partials,
-                                              scal + kOffNrm, s, Q32));
-                    PD_HIP(dev.fetch(kOffNrm, 1));
-                    nrm_v = dev.host[kOffNrm];
-                    ++info.reorth_second_passes;
+                PD_HIP(launch_update_project(Q, ld, k + 1, dim, scalars->c, nullptr, nullptr, pin, f32_step, 0.0, dst,
+                                             dst32, partials, nullptr, s, Q32, &step));
+                PD_HIP(launch_update_norm(Q, ld, k + 1, dim, scalars->c2, nullptr, dst, dst32, partials, nullptr, s, Q32,
+                                          &step));
+            }
+            if (!ends_wait(k, m, dim)) continue;
+            PD_HIP(dev.fetch(kOffAlpha, kOffBeta + k + 1 - kOffAlpha));
+            for (; taken <= k; ++taken) {
+                alpha[taken] = dev.host[kOffAlpha + taken];
+                beta[taken] = taken + 1 < m || taken == 0 ? dev.host[kOffBeta + taken] : 0.0;
+                tnorm = std::max(tnorm, std::fabs(alpha[taken]) + beta[taken]);
+                if (taken + 1 < m_eff && beta[taken] <= 1e-14 * std::max(tnorm, 1e-300)) {
+                    m_eff = taken + 1;   // invariant subspace: the Ritz pair is exact
+                    info.iterations -= k - taken;
+                    if (y32) info.iterations_f32 -= k - taken;
                 }
-            } else {
-                PD_HIP(dev.fetch(kOffC + k, 1));
             }
-            if (time_products) {
-                float ms = 0.0f;
-                PD_HIP(hipEventElapsedTime(&ms, ev.a, ev.b));
-                (f32_step ? info.sigma_seconds_f32 : info.sigma_seconds_f64) += 1e-3 * ms;
-            }
-            alpha[k] = sigma + dev.host[kOffC + k];
-            beta[k] = std::sqrt(std::max(nrm_v, 0.0));
             if (k == 0) {
                 e0 = alpha[0];
                 residual = beta[0] / std::max(std::fabs(alpha[0]), 1e-3 * dscale);
@@ -380,19 +362,14 @@ pd_status lanczos_run(pd_basis b, const CoefBlock &host_coef, const pd_lanczos_o
                 if (residual <= o->tol) converged = true;
                 if (converged || final_check) break;
             }
-            if (!store) break;
-            double tnorm = 0.0;
-            for (int i = 0; i <= k; ++i) tnorm = std::max(tnorm, std::fabs(alpha[i]) + beta[i]);
-            if (beta[k] <= 1e-14 * std::max(tnorm, 1e-300)) {
-                m_eff = k + 1;  // invariant subspace: the Ritz pair is exact
-                break;
-            }
-            sc[k + 1] = 1.0 / beta[k];
+            if (m_eff < m) break;
+            PD_HIP(launch_stamp(scalars, s));
         }
         if (converged || final_check) break;
         if (tridiag_lowest(m_eff, alpha.data(), beta.data(), &theta, y.data()) != 0)
             return fail(PD_EDEVICE, "tridiagonal eigensolver failed (m=%d)", m_eff);
-        for (int j = 0; j < m_eff; ++j) yy[j] = y[j] * sc[j];
+        // q_j = (stored column j) / beta_{j-1}
+        for (int j = 0; j < m_eff; ++j) yy[j] = j > 0 ? y[j] * (1.0 / beta[j - 1]) : y[j];
         PD_HIP(launch_combine(Q, ld, m_eff, dim, yy.data(), w, partials, scal + kOffNrm, scal + kOffSum, s, Q32));
         PD_HIP(dev.fetch(kOffNrm, 1));
         double nr = std::sqrt(dev.host[kOffNrm]);
@@ -400,6 +377,15 @@ pd_status lanczos_run(pd_basis b, const CoefBlock &host_coef, const pd_lanczos_o
         PD_HIP(launch_scale(w, dim, 1.0 / nr, Q, nullptr, s));
         // Mode 1 (no restart) and the last allowed cycle only measure the Ritz vector next.
         if (o->mode == 1 || cycle >= o->max_restarts) final_check = true;
+    }
+    PD_HIP(dev.fetch(kOffAgain, 4));
+    info.reorth_second_passes = (int)dev.host[kOffAgain + 1];
+    if (time_products) {
+        int khz = 0, device = 0;
+        PD_HIP(hipGetDevice(&device));
+        if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || khz <= 0) khz = 100000;
+        info.sigma_seconds_f64 = dev.host[kOffAgain + 2] / (1e3 * khz);
+        info.sigma_seconds_f32 = dev.host[kOffAgain + 3] / (1e3 * khz);
     }
     info.restarts = cycle;
     info.converged = converged ? 1 : 0;

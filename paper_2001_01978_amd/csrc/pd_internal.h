@@ -245,6 +245,35 @@ hipError_t launch_sigma(int omega, int n, int64_t dim, const CoefBlock *coef, pd
 // has none.  Caller holds b->mu.
 pd_status ensure_plan(pd_basis b, hipStream_t s, const WinPlan **plan);
 
+// The scalars of a Lanczos cycle, kept on the device so that its steps can be
+// queued without waiting for one another: the kernels of a step read the
+// scales and recurrence terms here and the last of them writes the next ones.
+struct LanczosScalars {
+    double c[80];       // c = Q^T ps, then ||ps||^2 and ||H q_k||^2
+    double c2[66];      // c' = Q^T v, then ||v||^2
+    double again;       // 1: this step needs the second Gram-Schmidt pass
+    double passes;      // second passes so far
+    double ticks[2];    // device clock ticks spent in products (FP64, FP32)
+    double stamp;       // the clock when the kernel before a product ended
+    double pad0[41];
+    double nrm, sum;
+    double pad1[62];
+    double occ[62];
+    double alpha[64], beta[64], sc[65];   // q_j = sc[j] * (stored column j)
+    double pad2;
+};
+static_assert(sizeof(LanczosScalars) == 512 * sizeof(double), "the scalars' place in the workspace");
+// Step k of a cycle (its columns 0..k exist); theta: the Ritz value that stands
+// in for alpha_{-1}.
+struct LanczosStep {
+    LanczosScalars *s;   // device
+    int k;
+    double theta;
+    int f32;             // the product was FP32
+};
+// Sets the stamp where the host was waited for between two products.
+hipError_t launch_stamp(LanczosScalars *s, hipStream_t st);
+
 // vec.hip: Lanczos vector kernels.  Q holds columns of length dim with leading
 // dimension ld (elements).  `partials` is scratch of partial_doubles() doubles.
 int vec_grid();
@@ -254,24 +283,27 @@ size_t partial_doubles();
 // coefficients of stored columns subtracted first: ps = pf - sum_j d_j Qt_j.
 // out_dev[j] = q_j^T ps (j < ncols), out_dev[ncols] = ||ps||^2,
 // out_dev[ncols + 1] = ||pf||^2.
+// step (all of these): null, or the step whose scales and coefficients are on
+// the device; sp, sc_host and d_host are then not used, and the results go to its
+// scalars instead of out_dev.
 // Q32 (all of these): null, or the FP32 store of columns j >= 1 (column j at
 // Q32 + (j - 1) ld); column 0 is always FP64 at Q.  With Q32 the first FP32
 // column must hold finite values even when ncols == 1 (it is read with weight 0).
 hipError_t launch_project(const double *Q, int64_t ld, int ncols, int64_t dim, const void *p, bool p_f32, double sp,
                           const double *sc_host, const double *d_host, double *partials, double *out_dev,
-                          hipStream_t s, const float *Q32 = nullptr);
+                          hipStream_t s, const float *Q32 = nullptr, const LanczosStep *step = nullptr);
 // v = sp p - sum_j (d_j + c_dev[j] sc_j) Qt_j  ->  out (FP64, may be null) and
 // out32 (FP32, may be null); out_dev[j] = q_j^T v (j < ncols), out_dev[ncols] =
 // ||v||^2, both from the FP64 v.
 hipError_t launch_update_project(const double *Q, int64_t ld, int ncols, int64_t dim, const double *c_dev,
                                  const double *sc_host, const double *d_host, const void *p, bool p_f32, double sp,
                                  double *out, float *out32, double *partials, double *out_dev, hipStream_t s,
-                                 const float *Q32 = nullptr);
+                                 const float *Q32 = nullptr, const LanczosStep *step = nullptr);
 // v -= sum_j c_dev[j] q_j in place (and out32); nrm2_dev[0] = ||v||^2.  With v
 // null the vector is FP32 only and is updated in place in out32.
 hipError_t launch_update_norm(const double *Q, int64_t ld, int ncols, int64_t dim, const double *c_dev,
                               const double *sc_host, double *v, float *out32, double *partials, double *nrm2_dev,
-                              hipStream_t s, const float *Q32 = nullptr);
+                              hipStream_t s, const float *Q32 = nullptr, const LanczosStep *step = nullptr);
 // Up to 64 doubles passed to a kernel by value.
 struct SmallVec {
     double v[64];

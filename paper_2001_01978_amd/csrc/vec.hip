@@ -20,18 +20,41 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// The wave's sums of v[0..N), N <= 64: the return value is the one of index
+// `which` (negative: none) in the lane.  Every step halves the number of values: a
+// lane keeps one half and passes the other on to its partner, OFF lanes away, which
+// keeps that one.  That takes about N shuffles where a tree for each value takes 6 N.
+template <int N, int OFF>
+__device__ __forceinline__ double halve_sums(const double (&v)[N], int &which) {
+    if constexpr (N == 1) {
+        double t = v[0];
+#pragma unroll
+        for (int o = OFF; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+        which = 0;
+        return t;
+    } else {
+        constexpr int H = (N + 1) / 2;
+        const bool up = (threadIdx.x & OFF) != 0;
+        double w[H];
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const double hi = i + H < N ? v[i + H < N ? i + H : 0] : 0.0;
+            w[i] = (up ? hi : v[i]) + __shfl_xor(up ? v[i] : hi, OFF, 64);
+        }
+        const double t = halve_sums<H, OFF / 2>(w, which);
+        if (up) which = which >= 0 && which + H < N ? which + H : -1;
+        return t;
+    }
+}
+
 // Reduce acc[0..ncols) over the block; thread j < ncols writes partials[j*gridDim + block].
 template <int KMAX>
 __device__ __forceinline__ void block_partials(const double (&acc)[KMAX], int ncols, double *sh,
                                                double *__restrict__ partials) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-        if (j < ncols) {
-            double v = wave_sum(acc[j]);
-            if (lane == 0) sh[wid * KMAX + j] = v;
-        }
-    }
+    const int wid = threadIdx.x >> 6;
+    int j;
+    const double v = halve_sums<KMAX, 32>(acc, j);
+    if (j >= 0) sh[wid * KMAX + j] = v;
     __syncthreads();
     if ((int)threadIdx.x < ncols) {
         double s = 0.0;
@@ -48,13 +71,9 @@ __device__ __forceinline__ void block_partials_extra(const double (&acc)[KMAX], 
                                                      int ncols, double *sh, double *__restrict__ partials) {
     constexpr int W = KMAX + NX;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < KMAX; ++j) {
-        if (j < ncols) {
-            double v = wave_sum(acc[j]);
-            if (lane == 0) sh[wid * W + j] = v;
-        }
-    }
+    int j;
+    const double t = halve_sums<KMAX, 32>(acc, j);
+    if (j >= 0 && j < ncols) sh[wid * W + j] = t;
 #pragma unroll
     for (int x = 0; x < NX; ++x) {
         double v = wave_sum(extra[x]);
@@ -112,6 +131,15 @@ __device__ __forceinline__ void load_cols(const double *__restrict__ Q, const fl
     }
 }
 
+// Coefficient j of the recurrence terms known before step k's projection,
+// sigma_k q_k + beta_{k-1} q_{k-1} with sigma_k = alpha_{k-1} (theta at k = 0).
+__device__ __forceinline__ double step_sigma(const LanczosStep &st) {
+    return st.k > 0 ? st.s->alpha[st.k - 1] : st.theta;
+}
+__device__ __forceinline__ double step_d(const LanczosStep &st, int j) {
+    return j == st.k ? step_sigma(st) * st.s->sc[j] : j + 1 == st.k ? st.s->beta[j] * st.s->sc[j] : 0.0;
+}
+
 // With pf = sp * p and ps = pf - sum_j d_j Qt_j (d: the part of the
 // three-term recurrence known in advance), partials: raw_j = sum_i Qt_j[i]
 // ps[i] (j < ncols), sum_i ps[i]^2 (row ncols), sum_i pf[i]^2 (row ncols + 1).
@@ -119,13 +147,16 @@ template <int KMAX, typename TIn, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void project_kernel(const double *__restrict__ Q, int64_t ld, int ncols,
                                                            int64_t dim, const TIn *__restrict__ p, double sp,
                                                            SmallVec d, double *__restrict__ partials,
-                                                           const float *__restrict__ Q32) {
+                                                           const float *__restrict__ Q32, LanczosStep step) {
     __shared__ double sh[kWaves * (KMAX + 2)];
+    if (step.s && blockIdx.x == 0 && threadIdx.x == 0 && step.s->sc[step.k] != 0.0)
+        step.s->ticks[step.f32] += (double)wall_clock64() - step.s->stamp;
     double acc[KMAX], dj[KMAX], nrm[2] = {0.0, 0.0};
+    if (step.s) sp = step.s->sc[step.k];
 #pragma unroll
     for (int j = 0; j < KMAX; ++j) {
         acc[j] = 0.0;
-        dj[j] = (j < ncols) ? d.v[j] : 0.0;
+        dj[j] = (j < ncols) ? (step.s ? step_d(step, j) : d.v[j]) : 0.0;
     }
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < dim; i += stride) {
@@ -153,12 +184,13 @@ __global__ __launch_bounds__(kThreads) void update_project_kernel(const double *
                                                                   double sp, double *__restrict__ out,
                                                                   float *__restrict__ out32,
                                                                   double *__restrict__ partials,
-                                                                  const float *__restrict__ Q32) {
+                                                                  const float *__restrict__ Q32, LanczosStep step) {
     __shared__ double sh[kWaves * (KMAX + 1)];
     double cj[KMAX], acc[KMAX], nrm[1] = {0.0};
+    if (step.s) sp = step.s->sc[step.k];
 #pragma unroll
     for (int j = 0; j < KMAX; ++j) {
-        cj[j] = (j < ncols) ? d.v[j] + c[j] * sc.v[j] : 0.0;
+        cj[j] = (j < ncols) ? (step.s ? step_d(step, j) + c[j] * step.s->sc[j] : d.v[j] + c[j] * sc.v[j]) : 0.0;
         acc[j] = 0.0;
     }
     const int64_t stride = (int64_t)gridDim.x * kThreads;
@@ -184,11 +216,12 @@ __global__ __launch_bounds__(kThreads) void update_norm_kernel(const double *__r
                                                                const double *__restrict__ c, SmallVec sc,
                                                                double *v_io, float *out32,
                                                                double *__restrict__ partials,
-                                                               const float *__restrict__ Q32) {
+                                                               const float *__restrict__ Q32, LanczosStep step) {
     __shared__ double sh[kWaves * 1];
+    if (step.s && step.s->again == 0.0) return;
     double cj[KMAX];
 #pragma unroll
-    for (int j = 0; j < KMAX; ++j) cj[j] = (j < ncols) ? c[j] * sc.v[j] : 0.0;
+    for (int j = 0; j < KMAX; ++j) cj[j] = (j < ncols) ? c[j] * (step.s ? step.s->sc[j] : sc.v[j]) : 0.0;
     double acc[1] = {0.0};
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < dim; i += stride) {
@@ -336,11 +369,20 @@ __global__ __launch_bounds__(kThreads) void occupations_kernel(int omega, int n,
     block_partials<MAXW>(acc, omega, sh, partials);
 }
 
-inline unsigned grid_for(int64_t dim) {
+inline unsigned grid_for(int64_t dim, int cap = kGrid) {
     int64_t g = (dim + kThreads - 1) / kThreads;
-    if (g > kGrid) g = kGrid;
+    if (g > cap) g = cap;
     if (g < 1) g = 1;
     return (unsigned)g;
+}
+
+// Blocks of the kernels that hold a column's coefficient, sum and element in
+// registers: no more than are resident at their register counts (8, 5, 4, 3 and 2
+// waves per SIMD), so that no last round of them is nearly empty.  At 24 orbits
+// (2.7e6 rows, 20 columns) 768 blocks for all of them gave 49.5 ms per solve
+// against 50.8 with 2048, and at 28 orbits 416 against 422.
+inline unsigned grid_cols(int64_t dim, int ncols) {
+    return grid_for(dim, ncols <= 8 ? kGrid : ncols <= 12 ? 1280 : ncols <= 16 ? 1024 : ncols <= 24 ? 768 : 512);
 }
 
 // out[j] = sc_j * sum_b partials[j*nb + b], j < nout.
@@ -364,6 +406,69 @@ __global__ __launch_bounds__(kThreads) void finalize_scaled_kernel(const double 
     }
 }
 
+// The sum of column j's partial sums, in every thread of the workgroup.
+__device__ __forceinline__ double sum_partials(const double *__restrict__ partials, int nb, int j, double *sh) {
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nb; b += kThreads) s += partials[(size_t)j * nb + b];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    double t = 0.0;
+    for (int w = 0; w < kWaves; ++w) t += sh[w];
+    return t;
+}
+
+// Thresholds of the second Gram-Schmidt pass: ||v|| < ||ps|| / sqrt(2) or
+// ||v|| < ||H q_k|| / 128 (squared).
+constexpr double kReorthEta2 = 0.70710678118654752 * 0.70710678118654752;
+constexpr double kReorthTau2 = (1.0 / 128.0) * (1.0 / 128.0);
+
+// v = beta q_{k+1}.  A vanished v (an invariant subspace: the host ends the cycle
+// there) gets scale 0, so that the steps already queued behind it stay finite.
+__device__ __forceinline__ void step_norm(const LanczosStep &st, double nrm_v) {
+    const double beta = sqrt(fmax(nrm_v, 0.0));
+    double tnorm = 0.0;
+    for (int i = 0; i < st.k; ++i) tnorm = fmax(tnorm, fabs(st.s->alpha[i]) + st.s->beta[i]);
+    tnorm = fmax(tnorm, fabs(st.s->alpha[st.k]) + beta);
+    st.s->beta[st.k] = beta;
+    st.s->sc[st.k + 1] = beta <= 1e-14 * fmax(tnorm, 1e-300) || st.s->sc[st.k] == 0.0 ? 0.0 : 1.0 / beta;
+}
+
+// Behind a step's projection (WHAT 0), update (1) and second pass (2): one
+// workgroup per sum (0: ncols + 2, 1: ncols + 1, 2: 1).
+template <int WHAT>
+__global__ __launch_bounds__(kThreads) void step_kernel(const double *__restrict__ partials, int nb, LanczosStep st) {
+    __shared__ double sh[kWaves];
+    const int j = blockIdx.x, ncols = st.k + 1;
+    if (WHAT == 2 && st.s->again == 0.0) {
+        if (threadIdx.x == 0) st.s->stamp = (double)wall_clock64();
+        return;
+    }
+    const double t = sum_partials(partials, nb, j, sh);
+    if (threadIdx.x != 0) return;
+    if (WHAT == 0) {
+        const double c = j < ncols ? st.s->sc[j] * t : t;
+        st.s->c[j] = c;
+        if (j == st.k) st.s->alpha[j] = step_sigma(st) + c;
+    } else if (WHAT == 1) {
+        if (j < ncols) {
+            st.s->c2[j] = st.s->sc[j] * t;
+        } else {
+            st.s->c2[j] = t;
+            const double ps = st.s->c[ncols], hq = st.s->c[ncols + 1];
+            const bool again = st.s->sc[st.k] != 0.0 && !(t >= kReorthEta2 * ps && t >= kReorthTau2 * hq);
+            st.s->again = again ? 1.0 : 0.0;
+            if (!again) step_norm(st, t);
+        }
+    } else {
+        step_norm(st, t);
+        st.s->passes += 1.0;
+        st.s->stamp = (double)wall_clock64();
+    }
+}
+
+__global__ void stamp_kernel(LanczosScalars *s) { s->stamp = (double)wall_clock64(); }
+
 hipError_t finalize(const double *partials, unsigned nb, int ncols, double scale, double *out, hipStream_t s) {
     hipLaunchKernelGGL(finalize_kernel, dim3(ncols), dim3(kThreads), 0, s, partials, (int)nb, scale, out);
     return hipGetLastError();
@@ -380,13 +485,16 @@ hipError_t finalize(const double *partials, unsigned nb, int ncols, double scale
         else if ((ncols) <= 48) hipLaunchKernelGGL(KERNEL<48>, __VA_ARGS__);                     \
         else hipLaunchKernelGGL(KERNEL<64>, __VA_ARGS__);                                        \
     } while (0)
-// Same, for kernels templated on the column bound and the input type.
+// Same, for kernels templated on the column bound and the input type.  20 is the
+// default cycle: with 24 slots its last steps load 4 columns twice (80 against 85 us
+// at 24 orbits).
 #define PD_DISPATCH_COLS_T(ncols, T, KERNEL, ...)                                                 \
     do {                                                                                         \
         if ((ncols) <= 4) hipLaunchKernelGGL((KERNEL<4, T>), __VA_ARGS__);                       \
         else if ((ncols) <= 8) hipLaunchKernelGGL((KERNEL<8, T>), __VA_ARGS__);                  \
         else if ((ncols) <= 12) hipLaunchKernelGGL((KERNEL<12, T>), __VA_ARGS__);                \
         else if ((ncols) <= 16) hipLaunchKernelGGL((KERNEL<16, T>), __VA_ARGS__);                \
+        else if ((ncols) <= 20) hipLaunchKernelGGL((KERNEL<20, T>), __VA_ARGS__);                \
         else if ((ncols) <= 24) hipLaunchKernelGGL((KERNEL<24, T>), __VA_ARGS__);                \
         else if ((ncols) <= 32) hipLaunchKernelGGL((KERNEL<32, T>), __VA_ARGS__);                \
         else if ((ncols) <= 48) hipLaunchKernelGGL((KERNEL<48, T>), __VA_ARGS__);                \
@@ -400,6 +508,7 @@ hipError_t finalize(const double *partials, unsigned nb, int ncols, double scale
         else if ((ncols) <= 8) hipLaunchKernelGGL((KERNEL<8, B>), __VA_ARGS__);                  \
         else if ((ncols) <= 12) hipLaunchKernelGGL((KERNEL<12, B>), __VA_ARGS__);                \
         else if ((ncols) <= 16) hipLaunchKernelGGL((KERNEL<16, B>), __VA_ARGS__);                \
+        else if ((ncols) <= 20) hipLaunchKernelGGL((KERNEL<20, B>), __VA_ARGS__);                \
         else if ((ncols) <= 24) hipLaunchKernelGGL((KERNEL<24, B>), __VA_ARGS__);                \
         else if ((ncols) <= 32) hipLaunchKernelGGL((KERNEL<32, B>), __VA_ARGS__);                \
         else if ((ncols) <= 48) hipLaunchKernelGGL((KERNEL<48, B>), __VA_ARGS__);                \
@@ -418,27 +527,37 @@ hipError_t finalize_scaled(const double *partials, unsigned nb, int nout, const 
 int vec_grid() { return kGrid; }
 size_t partial_doubles() { return (size_t)kGrid * (kMaxCols + 2); }
 
+hipError_t launch_stamp(LanczosScalars *s, hipStream_t st) {
+    hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(1), 0, st, s);
+    return hipGetLastError();
+}
+
 hipError_t launch_project(const double *Q, int64_t ld, int ncols, int64_t dim, const void *p, bool p_f32, double sp,
                           const double *sc_host, const double *d_host, double *partials, double *out_dev,
-                          hipStream_t s, const float *Q32) {
+                          hipStream_t s, const float *Q32, const LanczosStep *step) {
     if (ncols < 1 || ncols > kMaxCols) return hipErrorInvalidValue;
-    unsigned nb = grid_for(dim);
+    unsigned nb = grid_cols(dim, ncols);
+    const LanczosStep st = step ? *step : LanczosStep{};
     SmallVec d;
-    for (int j = 0; j < 64; ++j) d.v[j] = j < ncols ? d_host[j] : 0.0;
+    for (int j = 0; j < 64; ++j) d.v[j] = !step && j < ncols ? d_host[j] : 0.0;
     if (p_f32 && Q32)
         PD_DISPATCH_COLS_T(ncols, float PD_COMMA true, project_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld, ncols,
-                           dim, static_cast<const float *>(p), sp, d, partials, Q32);
+                           dim, static_cast<const float *>(p), sp, d, partials, Q32, st);
     else if (p_f32)
         PD_DISPATCH_COLS_T(ncols, float PD_COMMA false, project_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld, ncols,
-                           dim, static_cast<const float *>(p), sp, d, partials, Q32);
+                           dim, static_cast<const float *>(p), sp, d, partials, Q32, st);
     else if (Q32)
         PD_DISPATCH_COLS_T(ncols, double PD_COMMA true, project_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld, ncols,
-                           dim, static_cast<const double *>(p), sp, d, partials, Q32);
+                           dim, static_cast<const double *>(p), sp, d, partials, Q32, st);
     else
         PD_DISPATCH_COLS_T(ncols, double PD_COMMA false, project_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld,
-                           ncols, dim, static_cast<const double *>(p), sp, d, partials, Q32);
+                           ncols, dim, static_cast<const double *>(p), sp, d, partials, Q32, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (step) {
+        hipLaunchKernelGGL(step_kernel<0>, dim3(ncols + 2), dim3(kThreads), 0, s, partials, (int)nb, st);
+        return hipGetLastError();
+    }
     ScaleVec f;
     for (int j = 0; j < kMaxCols + 2; ++j) f.v[j] = j < ncols ? sc_host[j] : 1.0;
     return finalize_scaled(partials, nb, ncols + 2, f, out_dev, s);
@@ -447,29 +566,34 @@ hipError_t launch_project(const double *Q, int64_t ld, int ncols, int64_t dim, c
 hipError_t launch_update_project(const double *Q, int64_t ld, int ncols, int64_t dim, const double *c_dev,
                                  const double *sc_host, const double *d_host, const void *p, bool p_f32, double sp,
                                  double *out, float *out32, double *partials, double *out_dev, hipStream_t s,
-                                 const float *Q32) {
+                                 const float *Q32, const LanczosStep *step) {
     if (ncols < 1 || ncols > kMaxCols) return hipErrorInvalidValue;
-    unsigned nb = grid_for(dim);
+    unsigned nb = grid_cols(dim, ncols);
+    const LanczosStep st = step ? *step : LanczosStep{};
     SmallVec sc, d;
     for (int j = 0; j < 64; ++j) {
-        sc.v[j] = j < ncols ? sc_host[j] : 0.0;
-        d.v[j] = j < ncols ? d_host[j] : 0.0;
+        sc.v[j] = !step && j < ncols ? sc_host[j] : 0.0;
+        d.v[j] = !step && j < ncols ? d_host[j] : 0.0;
     }
     if (p_f32 && Q32)
         PD_DISPATCH_COLS_T(ncols, float PD_COMMA true, update_project_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld,
-                           ncols, dim, c_dev, sc, d, static_cast<const float *>(p), sp, out, out32, partials, Q32);
+                           ncols, dim, c_dev, sc, d, static_cast<const float *>(p), sp, out, out32, partials, Q32, st);
     else if (p_f32)
         PD_DISPATCH_COLS_T(ncols, float PD_COMMA false, update_project_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld,
-                           ncols, dim, c_dev, sc, d, static_cast<const float *>(p), sp, out, out32, partials, Q32);
+                           ncols, dim, c_dev, sc, d, static_cast<const float *>(p), sp, out, out32, partials, Q32, st);
     else if (Q32)
         PD_DISPATCH_COLS_T(ncols, double PD_COMMA true, update_project_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld,
-                           ncols, dim, c_dev, sc, d, static_cast<const double *>(p), sp, out, out32, partials, Q32);
+                           ncols, dim, c_dev, sc, d, static_cast<const double *>(p), sp, out, out32, partials, Q32, st);
     else
         PD_DISPATCH_COLS_T(ncols, double PD_COMMA false, update_project_kernel, dim3(nb), dim3(kThreads), 0, s, Q,
                            ld, ncols, dim, c_dev, sc, d, static_cast<const double *>(p), sp, out, out32, partials,
-                           Q32);
+                           Q32, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (step) {
+        hipLaunchKernelGGL(step_kernel<1>, dim3(ncols + 1), dim3(kThreads), 0, s, partials, (int)nb, st);
+        return hipGetLastError();
+    }
     ScaleVec f;
     for (int j = 0; j < kMaxCols + 2; ++j) f.v[j] = j < ncols ? sc_host[j] : 1.0;
     return finalize_scaled(partials, nb, ncols + 1, f, out_dev, s);
@@ -477,20 +601,25 @@ hipError_t launch_update_project(const double *Q, int64_t ld, int ncols, int64_t
 
 hipError_t launch_update_norm(const double *Q, int64_t ld, int ncols, int64_t dim, const double *c_dev,
                               const double *sc_host, double *v, float *out32, double *partials, double *nrm2_dev,
-                              hipStream_t s, const float *Q32) {
+                              hipStream_t s, const float *Q32, const LanczosStep *step) {
     if (!v && !out32) return hipErrorInvalidValue;
     if (ncols < 1 || ncols > kMaxCols) return hipErrorInvalidValue;
-    unsigned nb = grid_for(dim);
+    unsigned nb = grid_cols(dim, ncols);
+    const LanczosStep st = step ? *step : LanczosStep{};
     SmallVec sc;
-    for (int j = 0; j < 64; ++j) sc.v[j] = j < ncols ? sc_host[j] : 0.0;
+    for (int j = 0; j < 64; ++j) sc.v[j] = !step && j < ncols ? sc_host[j] : 0.0;
     if (Q32)
         PD_DISPATCH_COLS_B(ncols, true, update_norm_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld, ncols, dim, c_dev,
-                           sc, v, out32, partials, Q32);
+                           sc, v, out32, partials, Q32, st);
     else
         PD_DISPATCH_COLS_B(ncols, false, update_norm_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld, ncols, dim,
-                           c_dev, sc, v, out32, partials, Q32);
+                           c_dev, sc, v, out32, partials, Q32, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (step) {
+        hipLaunchKernelGGL(step_kernel<2>, dim3(1), dim3(kThreads), 0, s, partials, (int)nb, st);
+        return hipGetLastError();
+    }
     return finalize(partials, nb, 1, 1.0, nrm2_dev, s);
 }
 
@@ -509,7 +638,7 @@ hipError_t launch_combine(const double *Q, int64_t ld, int ncols, int64_t dim, c
     if (ncols < 1 || ncols > kMaxCols) return hipErrorInvalidValue;
     SmallVec y;
     for (int j = 0; j < kMaxCols; ++j) y.v[j] = j < ncols ? y_host[j] : 0.0;
-    unsigned nb = grid_for(dim);
+    unsigned nb = grid_cols(dim, ncols);
     if (Q32)
         PD_DISPATCH_COLS_B(ncols, true, combine_kernel, dim3(nb), dim3(kThreads), 0, s, Q, ld, ncols, dim, y, out,
                            partials, Q32);
