@@ -170,6 +170,11 @@ __device__ __forceinline__ int64_t first_lane64(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+__device__ __forceinline__ int64_t lane64(int64_t v, int lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
 __device__ __forceinline__ int first_lane(int v) { return __builtin_amdgcn_readfirstlane(v); }
 template <typename T>
 using Global = T __attribute__((address_space(1))) *;
@@ -463,13 +468,17 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? (W == 8 ? 2 : W == 7 ? 3 :
         }
     }
     // Lanes whose base lies within 32 bits of the first one's go together
-    // (all of them except at the ends of very large spaces).
-    bool todo = true;
-    while (todo) {
-        const int64_t ub = first_lane64(base);
+    // (all of them except at the ends of very large spaces).  The loop's condition is the
+    // wave's, not the lane's: a loop that each lane left behind its own rows could have
+    // the rows moved behind it, where lanes of different ub meet again.
+    uint64_t pending = __ballot(1);
+    const int lane = threadIdx.x & 63;
+    while (pending) {
+        const int64_t ub = lane64(base, __builtin_ctzll(pending));
         const uint64_t rel = (uint64_t)(base - ub);
-        if ((rel + C.reach) * sizeof(T) <= 0xFFFFFFFFull) {
-            todo = false;
+        const bool mine = ((pending >> lane) & 1) && (rel + C.reach) * sizeof(T) <= 0xFFFFFFFFull;
+        const uint64_t taken = __ballot(mine);
+        if (mine) {
             switch (C.K) {
 #define PD_WIN_CASE(KK)                                                                                             \
     case KK:                                                                                                        \
@@ -480,6 +489,7 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? (W == 8 ? 2 : W == 7 ? 3 :
 #undef PD_WIN_CASE
             }
         }
+        pending &= ~taken;
     }
 }
 

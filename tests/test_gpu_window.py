@@ -78,3 +78,34 @@ def test_product_rounding(pdg, oracle_mod):
         y = b.sigma(eps, V, xt).cpu().numpy().astype(np.float64)
         # (FP32 also rounds the couplings: one more u per term)
         assert np.all(np.abs(y - want) <= (n * (om - n) + 4) * u * scale), dt
+
+
+@pytest.mark.parametrize("om,n", [(34, 17), (35, 17)])
+def test_every_row_of_a_far_space(pdg, om, n):
+    """Above 2^32 bytes the 64 lanes of a wave can lie further apart than a 32-bit offset
+    reaches (at 34 orbits in FP64 only, at 35 in FP32 too, at other places).  All terms of a
+    row are positive, so every row of the FP32 product is within (hops + 4) 2^-24 of the FP64 one."""
+    import gc
+    import torch
+    gc.collect()
+    torch.cuda.empty_cache()
+    rng = np.random.default_rng(om)
+    eps = rng.uniform(1.0, 3.0, om)
+    V = rng.uniform(0.1, 0.3, (om, om))
+    V = (V + V.T) / 2
+    b = pdg.Basis(om, n, store_states=False)
+    print(f"omega={om} n={n} dim={b.dim}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(om)
+    x = torch.rand(b.dim, dtype=torch.float32, device="cuda", generator=g).add_(0.5)
+    y32 = b.sigma(eps, V, x)
+    x = x.double()
+    y = b.sigma(eps, V, x)
+    del x
+    worst = 0.0
+    for i in range(0, b.dim, 1 << 27):
+        w = y[i:i + (1 << 27)]
+        worst = max(worst, float(((y32[i:i + (1 << 27)].double() - w).abs_() / w).max()))
+    print(f"worst relative difference {worst:.2e}", flush=True)
+    del y, y32, w
+    torch.cuda.empty_cache()
+    assert worst <= (n * (om - n) + 4) * 2.0 ** -24
