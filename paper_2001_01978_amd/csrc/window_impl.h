@@ -20,6 +20,14 @@
 //     same for all lanes, so a load's address is a scalar plus one register.
 // An element is loaded once for up to 16 hops, where a product with a
 // row per lane loads one per hop, and no address is computed per hop.
+//
+// Measured against a row per lane (32 orbits, 16 pairs, 6.0e8 rows x 256 hops, FP64):
+// 82.9 -> 26.4 ms; 28 orbits, 14 pairs (4.0e7 rows) 3.98 -> 1.57 ms; 31 orbits, 17 pairs
+// FP32 20.7 -> 6.25 ms.  Of the 26.4 ms the upper window takes 12.9, the next one 8.6
+// and the segments 4.9.  The windows are bound by the L1: an 8-byte load takes 16
+// of its cycles per wave at best and 22 here, 20 loads per row in the upper window and
+// 14 in the next one, and it is busy for 73 to 79% of the time; at the same time 65 and
+// 26 GB come from below the L2s, 5 and 3 TB/s.  The arithmetic alone would take 4 ms.
 #pragma once
 
 #include <type_traits>
@@ -27,21 +35,6 @@
 
 #include "pd_internal.h"
 
-#ifndef PD_BATCH
-#define PD_BATCH 14
-#endif
-#ifndef PD_B8
-#define PD_B8 10
-#endif
-#ifndef PD_B7
-#define PD_B7 9
-#endif
-#ifndef PD_B6
-#define PD_B6 8
-#endif
-#ifndef PD_XCDRUN
-#define PD_XCDRUN 64
-#endif
 namespace pd {
 namespace win {
 
@@ -193,10 +186,12 @@ __device__ __forceinline__ Global<T> at(Global<T> uniform, uint32_t byte_off) {
 }
 
 // Elements of a batch: a batch is asked for before the one ahead of it is
-// multiplied.  Two batches make a chunk of a tile.
+// multiplied.  Two batches make a chunk of a tile.  As many as the registers
+// hold beside the results without spilling (FP64, W = 8: 140 registers of results);
+// 7 or 12 instead of 10 were within 1% at 32 orbits.
 template <typename T, int W>
 constexpr int batch() {
-    return sizeof(T) == 4 ? PD_BATCH : W == 8 ? PD_B8 : W == 7 ? PD_B7 : W == 6 ? PD_B6 : 5;
+    return sizeof(T) == 4 ? 14 : W == 8 ? 10 : W == 7 ? 9 : W == 6 ? 8 : 5;
 }
 
 // Batch b of the tile of KP pairs on W orbits, of elements at xb + off[] + voff.
@@ -234,16 +229,17 @@ __device__ __forceinline__ void take_tile(Global<const T> xb, Const<int64_t> off
     });
 }
 
-// The hops between the window and the low orbits of one kind: steps low
-// orbits, found one by one by next(j, r'), each with the tile of KP pairs.  The
+// The hops between the window and the low orbits of one kind: low orbits
+// number from..to - 1, found one by one by next(j, r'), each with the tile of KP pairs.  The
 // tile is taken in chunks, all steps for one chunk before the next: the lanes
 // in flight then keep to kChunk rows of x for a while, which their XCD's L2 can
-// hold, and an element is read from it for most of its uses.
+// hold, and an element is read from it for most of its uses (32 orbits FP64, before
+// the segment pass took the lowest orbits: 44 ms tile by tile, 40 by chunks).
 template <typename T, int W, int K, int KP, typename Start, typename Next>
-__device__ __forceinline__ void take_steps(Global<const T> xb, Const<int64_t> off, uint32_t rel, int steps,
+__device__ __forceinline__ void take_steps(Global<const T> xb, Const<int64_t> off, uint32_t rel, int from, int to,
                                            const T *Vs, T (&acc)[cbinom(W, K)], Start &&start, Next &&next) {
     constexpr int kBatch = batch<T, W>(), kChunk = 2 * kBatch, N = cbinom(W, KP), NCH = (N + kChunk - 1) / kChunk;
-    if (steps <= 0) return;
+    if (from >= to) return;
     static_for<NCH>([&](auto cc) PD_INLINE {
         constexpr int b0 = decltype(cc)::value * kChunk, b1 = b0 + kBatch;
         constexpr int n0 = N - b0 < kBatch ? N - b0 : kBatch;
@@ -252,9 +248,10 @@ __device__ __forceinline__ void take_steps(Global<const T> xb, Const<int64_t> of
         int j;
         uint32_t rp;
         start();
-        next(0, j, rp);
+        for (int a = 0; a < from; ++a) next(a, j, rp);
+        next(from, j, rp);
         load_batch<T, W, KP, b0, n0>(xb, here(off), (rel + rp) * (uint32_t)sizeof(T), xv[0]);
-        for (int a = 0; a < steps; ++a) {
+        for (int a = from; a < to; ++a) {
             T v[W];
 #pragma unroll
             for (int i = 0; i < W; ++i) v[i] = Vs[j * W + i];
@@ -264,7 +261,7 @@ __device__ __forceinline__ void take_steps(Global<const T> xb, Const<int64_t> of
                 __builtin_amdgcn_sched_barrier(0);
                 take_batch<T, W, K, KP, b0, n0>(xv[0], v, acc);
                 __builtin_amdgcn_sched_barrier(0);
-                if (a + 1 < steps) {
+                if (a + 1 < to) {
                     next(a + 1, j, rp);
                     load_batch<T, W, KP, b0, n0>(xb, here(off), (rel + rp) * (uint32_t)sizeof(T), xv[0]);
                 }
@@ -275,7 +272,7 @@ __device__ __forceinline__ void take_steps(Global<const T> xb, Const<int64_t> of
 #pragma unroll
                 for (int i = 0; i < n0; ++i) xc[i] = xv[0][i];
                 take_batch<T, W, K, KP, b0, n0>(xc, v, acc);
-                if (a + 1 < steps) {
+                if (a + 1 < to) {
                     next(a + 1, j, rp);
                     load_batch<T, W, KP, b0, n0>(xb, here(off), (rel + rp) * (uint32_t)sizeof(T), xv[0]);
                 }
@@ -286,10 +283,13 @@ __device__ __forceinline__ void take_steps(Global<const T> xb, Const<int64_t> of
 }
 
 // The lane's (s, l): s as its base rank relative to xb / yb (a scalar base of
-// the wave), l as its rank r and its word.
-template <typename T, int W, int K>
+// the wave), l as its rank r and its word.  With PARTS = 2 two waves share the lanes'
+// work, as evenly as whole steps allow; the second (part 1) hands its sums over
+// in LDS, ex, which the slots of pre are a part of.
+template <typename T, int W, int K, int PARTS>
 __device__ __forceinline__ void window_rows(const WinArgs<T> &A, int nl, int q, int64_t ub, uint32_t rel, uint32_t r,
-                                            uint32_t lw, const uint32_t *Ct, int ks, const T *Vs, uint32_t *pre) {
+                                            uint32_t lw, const uint32_t *Ct, int ks, const T *Vs, uint32_t *pre,
+                                            int part, bool write, T *ex) {
     using TK = Tile<W, K>;
     constexpr int N = TK::N;
     T acc[N];
@@ -298,8 +298,21 @@ __device__ __forceinline__ void window_rows(const WinArgs<T> &A, int nl, int q, 
     const Const<int64_t> off = as_const(A.off) + ((int64_t)(q - A.qmin) << W);
     const Global<const T> xb = first_lane_ptr(A.x + ub);
 
+    // the steps of this part; the cost of a step is its tile's number of elements
+    const int ne = A.w0 - nl;
+    int o0 = 0, o1 = nl, e0 = 0, e1 = ne;
+    if constexpr (PARTS == 2) {
+        constexpr int inside = K > 0 && K < W ? N : 0, co = cbinom(W, K + 1), ce = cbinom(W, K - 1);
+        int left = ((inside + nl * co + ne * ce) >> 1) - inside;
+        const int ho = co > 0 ? max(0, min(nl, (left + co / 2) / (co > 0 ? co : 1))) : 0;
+        left -= ho * co;
+        const int he = ce > 0 && (ho == nl || co == 0) ? max(0, min(ne, (left + ce / 2) / (ce > 0 ? ce : 1))) : 0;
+        if (part == 0) o1 = ho, e1 = he;
+        else o0 = ho, e0 = he;
+    }
+
     // hops inside the window
-    if constexpr (K > 0 && K < W) {
+    if constexpr (K > 0 && K < W) if (part == 0) {
         const Const<T> V = as_const(A.V);
         T vw[W * W];
 #pragma unroll
@@ -321,13 +334,13 @@ __device__ __forceinline__ void window_rows(const WinArgs<T> &A, int nl, int q, 
             occ &= ~(1u << j);
             const uint32_t *c = Ct + j * ks + (nl - a);
             up += c[1] - c[0];
-            pre[(a + 1) * kBlock] = up;
+            pre[(a + 1) * (PARTS * kBlock)] = up;
         }
     }
     if constexpr (K < W) {
         uint32_t occ, down;
         take_steps<T, W, K, K + 1>(
-            xb, off, rel, nl, Vs, acc,
+            xb, off, rel, o0, o1, Vs, acc,
             [&]() PD_INLINE {
                 occ = lw;
                 down = 0;
@@ -345,16 +358,27 @@ __device__ __forceinline__ void window_rows(const WinArgs<T> &A, int nl, int q, 
     if constexpr (K > 0) {
         uint32_t emp;
         take_steps<T, W, K, K - 1>(
-            xb, off, rel, A.w0 - nl, Vs, acc,
+            xb, off, rel, e0, e1, Vs, acc,
             [&]() PD_INLINE { emp = ~lw & (A.w0 >= 32 ? ~0u : (1u << A.w0) - 1); },
             [&](int e, int &j, uint32_t &rp) PD_INLINE {
                 j = 31 - __clz((int)emp);
                 emp &= ~(1u << j);
                 const int a = A.w0 - 1 - j - e;   // occupied orbits above j
-                rp = r + Ct[j * ks + nl - a + 1] + pre[a * kBlock];
+                rp = r + Ct[j * ks + nl - a + 1] + pre[a * (PARTS * kBlock)];
             });
     }
 
+    if constexpr (PARTS == 2) {
+        __syncthreads();
+        if (part == 1) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) ex[i * kBlock] = acc[i];
+        }
+        __syncthreads();
+        if (part == 1 || !write) return;
+#pragma unroll
+        for (int i = 0; i < N; ++i) acc[i] += ex[i * kBlock];
+    }
     const Global<T> yb = first_lane_ptr(A.y + ub);
     const uint32_t vo = (rel + r) * (uint32_t)sizeof(T);
     constexpr int first = TK::first();
@@ -367,8 +391,9 @@ __device__ __forceinline__ void window_rows(const WinArgs<T> &A, int nl, int q, 
 
 // Workgroups go to the eight XCDs in turn; each XCD's are given a run of
 // kXcdRun neighbouring blocks, as many as it holds at once, so that the lanes
-// that share its L2 have neighbouring low states and read the same elements.
-constexpr uint32_t kXcdRun = PD_XCDRUN;
+// that share its L2 have neighbouring low states and read the same elements
+// (32 orbits: runs of 1, 32, 64 and 128 took 40.6, 39.8, 40.2 and 41.1 ms, then).
+constexpr uint32_t kXcdRun = 64;
 __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t grid) {
     constexpr uint32_t group = 8 * kXcdRun;
     const uint32_t g0 = b / group * group;
@@ -384,7 +409,7 @@ struct WinLds {
     size_t vs, ur, ub, pre, total;
 };
 template <typename T>
-__host__ __device__ inline WinLds win_lds(int n, int w0, int U, int W) {
+__host__ __device__ inline WinLds win_lds(int n, int w0, int U, int W, int parts) {
     WinLds L;
     const int nl = n < w0 ? n : w0, m = n < U ? n : U;
     L.ks = nl + 2;
@@ -398,14 +423,19 @@ __host__ __device__ inline WinLds win_lds(int n, int w0, int U, int W) {
     L.ur = o;
     o += (size_t)U * L.us * 4;
     L.pre = o;   // binomials of the low orbits, then the slots
-    o += (size_t)w0 * L.ks * 4 + (size_t)(nl + 1) * kBlock * 4;
+    o += (size_t)w0 * L.ks * 4 + (size_t)(nl + 1) * parts * kBlock * 4;
+    if (parts == 2) {   // the sums handed over, in the same place
+        const size_t e = L.pre + (size_t)cbinom(W, W / 2) * kBlock * sizeof(T);
+        if (o < e) o = e;
+    }
     L.total = o;
     return L;
 }
 
-template <typename T, int W>
-__global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? (W == 8 ? 2 : W == 7 ? 3 : 4) : (W == 8 ? 3 : 4)) void window_kernel(
-    WinArgs<T> A) {
+template <typename T, int W, int PARTS>
+__global__ __launch_bounds__(kBlock * PARTS, PARTS == 2 || (sizeof(T) == 8 && W == 8) ? 2
+                                             : sizeof(T) == 8 && W == 7 || W == 8     ? 3
+                                                                                      : 4) void window_kernel(WinArgs<T> A) {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t block = xcd_block(blockIdx.x, gridDim.x);
     // class of this workgroup
@@ -421,25 +451,28 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? (W == 8 ? 2 : W == 7 ? 3 :
     const Const<WinClass> cp = as_const(A.cls) + c;
     const WinClass C = {cp->first_block, cp->lanes, cp->NL, cp->reach, cp->K, cp->m, cp->nl, 0};
     const int nl = C.nl, m = C.m, q = A.n - m;
-    const WinLds L = win_lds<T>(A.n, A.w0, A.U, W);
+    const WinLds L = win_lds<T>(A.n, A.w0, A.U, W, PARTS);
     T *Vs = reinterpret_cast<T *>(smem + L.vs);
     uint64_t *Ub = reinterpret_cast<uint64_t *>(smem + L.ub);
     uint32_t *Ur = reinterpret_cast<uint32_t *>(smem + L.ur);
     uint32_t *Ct = reinterpret_cast<uint32_t *>(smem + L.pre);
     uint32_t *pre = Ct + A.w0 * L.ks + threadIdx.x;
-    for (int i = threadIdx.x; i < A.w0 * W; i += kBlock) Vs[i] = A.V[(A.w0 + i % W) * A.omega + i / W];
-    for (int i = threadIdx.x; i < A.U * L.us; i += kBlock) {
+    for (int i = threadIdx.x; i < A.w0 * W; i += kBlock * PARTS) Vs[i] = A.V[(A.w0 + i % W) * A.omega + i / W];
+    for (int i = threadIdx.x; i < A.U * L.us; i += kBlock * PARTS) {
         const int p = i / L.us, k = i - p * L.us;
         Ur[i] = (uint32_t)g_binom.v[p][k];
         Ub[i] = g_binom.v[A.w0 + W + p][q + k];
     }
-    for (int i = threadIdx.x; i < A.w0 * L.ks; i += kBlock) {
+    for (int i = threadIdx.x; i < A.w0 * L.ks; i += kBlock * PARTS) {
         const int p = i / L.ks, k = i - p * L.ks;
         Ct[i] = (uint32_t)g_binom.v[p][k];
     }
     __syncthreads();
-    const uint32_t f = (block - C.first_block) * kBlock + threadIdx.x;
-    if (f >= C.lanes) return;
+    const int part = PARTS == 2 ? first_lane((int)(threadIdx.x / kBlock)) : 0;
+    uint32_t f = (block - C.first_block) * kBlock + threadIdx.x % kBlock;
+    const bool write = f < C.lanes;
+    if (PARTS == 2) f = write ? f : C.lanes - 1;   // barriers ahead
+    else if (!write) return;
     const uint32_t si = f / C.NL, r = f - si * C.NL;
     // base of the upper state of rank si
     int64_t base = 0;
@@ -467,29 +500,36 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? (W == 8 ? 2 : W == 7 ? 3 :
             lw |= take ? (1u << p) : 0u;
         }
     }
-    // Lanes whose base lies within 32 bits of the first one's go together
-    // (all of them except at the ends of very large spaces).  The loop's condition is the
-    // wave's, not the lane's: a loop that each lane left behind its own rows could have
-    // the rows moved behind it, where lanes of different ub meet again.
-    uint64_t pending = __ballot(1);
-    const int lane = threadIdx.x & 63;
-    while (pending) {
-        const int64_t ub = lane64(base, __builtin_ctzll(pending));
-        const uint64_t rel = (uint64_t)(base - ub);
-        const bool mine = ((pending >> lane) & 1) && (rel + C.reach) * sizeof(T) <= 0xFFFFFFFFull;
-        const uint64_t taken = __ballot(mine);
-        if (mine) {
-            switch (C.K) {
+    T *ex = reinterpret_cast<T *>(smem + L.pre) + threadIdx.x % kBlock;
+    auto rows = [&](int64_t ub, uint32_t rel) PD_INLINE {
+        switch (C.K) {
 #define PD_WIN_CASE(KK)                                                                                             \
     case KK:                                                                                                        \
-        if constexpr (KK <= W) window_rows<T, W, KK>(A, nl, q, ub, (uint32_t)rel, r, lw, Ct, L.ks, Vs, pre);        \
+        if constexpr (KK <= W)                                                                                      \
+            window_rows<T, W, KK, PARTS>(A, nl, q, ub, rel, r, lw, Ct, L.ks, Vs, pre, part, write, ex);             \
         break;
-                PD_WIN_CASE(0) PD_WIN_CASE(1) PD_WIN_CASE(2) PD_WIN_CASE(3) PD_WIN_CASE(4) PD_WIN_CASE(5)
-                PD_WIN_CASE(6) PD_WIN_CASE(7) PD_WIN_CASE(8)
+            PD_WIN_CASE(0) PD_WIN_CASE(1) PD_WIN_CASE(2) PD_WIN_CASE(3) PD_WIN_CASE(4) PD_WIN_CASE(5)
+            PD_WIN_CASE(6) PD_WIN_CASE(7) PD_WIN_CASE(8)
 #undef PD_WIN_CASE
-            }
         }
-        pending &= ~taken;
+    };
+    if constexpr (PARTS == 2) {
+        rows(0, (uint32_t)base);   // fewer than kSplitBlocks * 256 * 70 states
+    } else {
+        // Lanes whose base lies within 32 bits of the first one's go together
+        // (all of them except at the ends of very large spaces).  The loop's condition is
+        // the wave's, not the lane's: a loop that each lane left behind its own rows
+        // could have the rows moved behind it, where lanes of different ub meet again.
+        uint64_t pending = __ballot(1);
+        const int lane = threadIdx.x & 63;
+        while (pending) {
+            const int64_t ub = lane64(base, __builtin_ctzll(pending));
+            const uint64_t rel = (uint64_t)(base - ub);
+            const bool mine = ((pending >> lane) & 1) && (rel + C.reach) * sizeof(T) <= 0xFFFFFFFFull;
+            const uint64_t taken = __ballot(mine);
+            if (mine) rows(ub, (uint32_t)rel);
+            pending &= ~taken;
+        }
     }
 }
 
@@ -503,6 +543,9 @@ __global__ __launch_bounds__(kBlock, sizeof(T) == 8 ? (W == 8 ? 2 : W == 7 ? 3 :
 // Short segments of one pair count go through LDS together, as a group.
 // While an FP64 segment is worked on, the next one is on its way into registers;
 // in FP32 two workgroups share a CU, and one loads while the other works.
+// Bound by LDS reads: about 29 per row, 4 cycles per wave and FP64 read, 20 us for a segment
+// of 12870 rows.  It replaced a third window of 8 and an 8-orbit pass: 40 -> 28.8 ms at
+// 32 orbits (FP64), and groups of short segments made that 26.3.
 constexpr int kSegThreads = 512;
 constexpr int kSegFetch = (12870 + kSegThreads - 1) / kSegThreads;
 
@@ -803,6 +846,12 @@ __global__ __launch_bounds__(kSegThreads, sizeof(T) == 8 ? 2 : 4) void segment_k
     }
 }
 
+// A pass of fewer workgroups leaves wave slots empty (a CU holds two of W = 8 in
+// FP64): two waves then share the lanes of each.  24 orbits, 12 pairs (257 workgroups): the
+// product takes 97.9 / 77.6 us (FP64 / FP32) so and 104 / 87 without; 23 orbits, 11 pairs
+// 66.7 / 54.4 and 71.8 / 60.3.  From 512 on, the slots are taken either way.
+constexpr uint32_t kSplitBlocks = 512;
+
 template <typename T, int W>
 hipError_t launch_window(const WinPass &ps, int omega, int n, const T *x, T *y, const T *V, hipStream_t s) {
     WinArgs<T> A;
@@ -817,8 +866,20 @@ hipError_t launch_window(const WinPass &ps, int omega, int n, const T *x, T *y, 
     A.x = x;
     A.y = y;
     A.V = V;
-    const size_t lds = win_lds<T>(n, A.w0, A.U, W).total;
-    hipLaunchKernelGGL((window_kernel<T, W>), dim3(ps.nblocks), dim3(kBlock), lds, s, A);
+    if constexpr (W >= 7) {
+        if (ps.nblocks < kSplitBlocks) {
+            const size_t lds = win_lds<T>(n, A.w0, A.U, W, 2).total;
+            hipError_t e = hipSuccess;
+            if (lds > 64 * 1024)
+                e = hipFuncSetAttribute(reinterpret_cast<const void *>(&window_kernel<T, W, 2>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 1024);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((window_kernel<T, W, 2>), dim3(ps.nblocks), dim3(2 * kBlock), lds, s, A);
+            return hipGetLastError();
+        }
+    }
+    const size_t lds = win_lds<T>(n, A.w0, A.U, W, 1).total;
+    hipLaunchKernelGGL((window_kernel<T, W, 1>), dim3(ps.nblocks), dim3(kBlock), lds, s, A);
     return hipGetLastError();
 }
 
