@@ -4,8 +4,8 @@
 Workload: the large random family at Omega=32, n=16 (601,080,390 states,
 256 pair hops per row), eps ~ U[0, 32), G_ij = 0.3(1 + 0.2u), seed 0.
 
-One step is one FP64 product y = Hx over the whole space (pd_sigma: unranking,
-diagonal, every pair hop located by its rank, Sec. 3.3), the operation a
+One step is one FP64 product y = Hx over the whole space (pd_sigma: diagonal
+and every pair hop, located by its rank, Sec. 3.3), the operation a
 Lanczos iteration spends its time in (Sec. 5.3); FP64 is the paper's
 arithmetic.  x is a seeded random vector already resident in HBM.  W untimed
 products, then K timed products bracketed by device synchronisations, each
@@ -41,10 +41,9 @@ PEAK_HBM_GBS = 8000.0
 # 32-bit VALU lane operations per second: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 # (one wave64 instruction per SIMD every 4 cycles; an FMA counted as one op).
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
-# Algorithmic VALU work per non-zero of the prefix-delta product: target rank =
-# rank + A + B (2 adds), up/down choice (compare + select), gather address,
-# coefficient address, FMA.
-OPS_PER_NONZERO = 7
+# Algorithmic VALU work per non-zero of the windowed product: the FMA (elements and
+# addresses are shared by up to 16 non-zeros).
+OPS_PER_NONZERO = 1
 METRIC = "sigma nonzeros/s + HBM GB/s; time-to-E0 at Omega=32,n=16, plain vs mixed vs warm"
 
 T_START = time.perf_counter()
@@ -96,7 +95,7 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = ["paper_2001_01978_amd/csrc/sigma_impl.h"]
+KERNEL_SOURCES = ["paper_2001_01978_amd/csrc/window_impl.h"]
 COUNTERS = "sigma_omega{om}_n{n}_counters"
 PIPELINE = "sigma_omega{om}_n{n}_pipeline_counters"
 CLOCK_HZ, N_CU, N_SIMD = 2.4e9, 256, 1024
@@ -129,7 +128,7 @@ def code_tokens(text):
 
 
 def kernel_source_hash():
-    """First 16 hex digits of the SHA-256 of the product kernel's code
+    """First 16 hex digits of the SHA-256 of the product kernels' code
     (comments and layout excluded): the counter summaries carry the hash of
     the source they were taken on."""
     import hashlib
@@ -516,7 +515,7 @@ def run(args, torch, np, inputs, pairdiag, om, n, eps, V, K, D):
         return {"bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": ach / PEAK_HBM_GBS if ach else None, "traffic": dram,
                 "kernel": kernel, "avg_launch_ms": avg * 1e3, "launches_timed": args.steps,
-                "achieved_is": "HBM bytes per launch (rocprofv3 FETCH_SIZE x copy-calibrated read scale + "
+                "achieved_is": "HBM bytes per product (rocprofv3 FETCH_SIZE x copy-calibrated read scale + "
                                "WRITE_SIZE, profiles/" + COUNTERS.format(om=om, n=n) + ".txt) / mean HIP-event "
                                "launch time in this run; FETCH_SIZE counts every byte the L2s fetch from below "
                                "them, hits in the 256 MB Infinity Cache included, so it bounds true HBM traffic "
@@ -534,9 +533,9 @@ def run(args, torch, np, inputs, pairdiag, om, n, eps, V, K, D):
                          "frac": D * K * OPS_PER_NONZERO / avg / 1e12 / PEAK_VALU_TOPS},
                 "nnz_per_s": D * K / avg}
 
-    OUT["roofline"] = roof(avg64, 8, "hbm_bytes_per_launch_f64", "sigma_kernel<uint32,double,16> (FP64 product)")
+    OUT["roofline"] = roof(avg64, 8, "hbm_bytes_per_launch_f64", "segment_kernel<double>, window_kernel<double,8> twice (FP64 product)")
     OUT["roofline"]["pipeline"] = pipeline(avg64, "f64")
-    OUT["roofline_f32"] = roof(avg32, 4, "hbm_bytes_per_launch_f32", "sigma_kernel<uint32,float,16> (FP32 product)")
+    OUT["roofline_f32"] = roof(avg32, 4, "hbm_bytes_per_launch_f32", "segment_kernel<float>, window_kernel<float,8> twice (FP32 product)")
     OUT["roofline_f32"]["pipeline"] = pipeline(avg32, "f32")
 
     # ---- time-to-E0: plain FP64, mixed, warm (once each)

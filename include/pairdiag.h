@@ -62,8 +62,9 @@ const char *pd_last_error(void);
 
 /* ------------------------------------------------------------------ basis
  * Sec. 3.1 (basis generation, Alg. conversion) and Sec. 3.2 (Eq. hash).
- * A basis handle describes the space (omega, n) and carries a small
- * coefficient block used by pd_sigma.  With store_states != 0 the library also
+ * A basis handle describes the space (omega, n) and carries small
+ * coefficient blocks used by pd_sigma and, for large spaces, the plan of its
+ * windowed product.  With store_states != 0 the library also
  * writes the ascending array of occupation bitstrings (uint64, bit i =
  * orbit i) into the caller buffer; sigma and the Lanczos driver never read it
  * (they recover states from ranks on the fly), so large spaces may skip it.
@@ -116,11 +117,13 @@ pd_status pd_basis_unrank(pd_basis b, const int64_t *ranks_dev, int64_t count,
  * pd_occupations act on the truncated space (H restricted to it: hops to
  * states left out are dropped).  A hop target is located by its full-space
  * rank (Sec. 3.2) and then mapped to its row: index_mode PD_TRUNC_BITMAP uses
- * one 16-byte word per 64 full ranks (which are kept, how many kept before);
+ * one 16-byte word per 64 full ranks (which are kept, how many kept before), or,
+ * below 2^32 full ranks and in the same place, a 4-byte cell per 16 and a count per
+ * 65536;
  * PD_TRUNC_BSEARCH binary-searches the ascending kept ranks, as the paper
  * does for truncated spaces.  dev_buf: device, 256-byte aligned,
  * pd_basis_truncated_bytes(omega, n, info) bytes (full dim / 4 bytes for the
- * words, 4 or 8 bytes per kept state for its full rank: 4 when
+ * words or cells, 4 or 8 bytes per kept state for its full rank: 4 when
  * C(omega, n) < 2^32).  pd_basis_rank, pd_basis_unrank and pd_warm_start
  * reject truncated handles.  Synchronises `stream`.
  *
@@ -175,8 +178,10 @@ pd_status pd_basis_truncation(pd_basis b, int *truncated, int64_t *full_dim);
 pd_status pd_sigma(pd_basis b, const double *eps, const double *V, pd_dtype dt,
                    const void *x_dev, void *y_dev, hipStream_t stream);
 
-/* Launch shape of pd_sigma on the space (omega, n) in precision dt, without
- * running anything (an implementation detail, not a passage of the paper):
+/* Launch shape of the row-per-lane kernel on the space (omega, n) in precision
+ * dt (pd_sigma takes it where neither the windowed product of large spaces nor the
+ * one-tile kernel of small ones applies), without running anything (an
+ * implementation detail, not a passage of the paper):
  * *threads = threads per workgroup (256 or 512), *lds_bytes = its dynamic
  * LDS, *lds_limit_bytes = the LDS limit the kernel runs under (the
  * instantiation's attribute above the default 64 KB, else that default);

@@ -24,10 +24,10 @@
 // Measured against a row per lane (32 orbits, 16 pairs, 6.0e8 rows x 256 hops, FP64):
 // 82.9 -> 26.4 ms; 28 orbits, 14 pairs (4.0e7 rows) 3.98 -> 1.57 ms; 31 orbits, 17 pairs
 // FP32 20.7 -> 6.25 ms.  Of the 26.4 ms the upper window takes 12.9, the next one 8.6
-// and the segments 4.9.  The windows are bound by the L1: an 8-byte load takes 16
-// of its cycles per wave at best and 22 here, 20 loads per row in the upper window and
-// 14 in the next one, and it is busy for 73 to 79% of the time; at the same time 65 and
-// 26 GB come from below the L2s, 5 and 3 TB/s.  The arithmetic alone would take 4 ms.
+// and the segments 4.9.  The windows are bound by the address path of the L1: 26 and
+// 18 loads per row and 27 and 25 cycles per load (a contiguous 8-byte load of 64
+// lanes takes 16), 85% and 80% of the time; at the same time 65 and 26 GB come from below
+// the L2s, 5 and 3 TB/s.  The arithmetic alone would take 4 ms.
 #pragma once
 
 #include <type_traits>
@@ -543,8 +543,8 @@ __global__ __launch_bounds__(kBlock * PARTS, PARTS == 2 || (sizeof(T) == 8 && W 
 // Short segments of one pair count go through LDS together, as a group.
 // While an FP64 segment is worked on, the next one is on its way into registers;
 // in FP32 two workgroups share a CU, and one loads while the other works.
-// Bound by LDS reads: about 29 per row, 4 cycles per wave and FP64 read, 20 us for a segment
-// of 12870 rows.  It replaced a third window of 8 and an 8-orbit pass: 40 -> 28.8 ms at
+// Bound by LDS reads: 45 per row, 4 cycles per wave and FP64 read, 2.8 of 4.9 ms at 32
+// orbits.  It replaced a third window of 8 and an 8-orbit pass: 40 -> 28.8 ms at
 // 32 orbits (FP64), and groups of short segments made that 26.3.
 constexpr int kSegThreads = 512;
 constexpr int kSegFetch = (12870 + kSegThreads - 1) / kSegThreads;
