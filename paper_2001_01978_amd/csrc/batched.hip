@@ -415,12 +415,14 @@ __device__ void solve_instance(const Args &A, const Instance &I, double *slot, T
                 }
             }
             const double beta = sqrt(fmax(nrm_v, 0.0));
-            __syncthreads();
             if (threadIdx.x == 0) {
                 sh.alpha[k] = alpha;
                 sh.beta[k] = beta;
                 if (store && beta > 0.0) sh.sc[k + 1] = 1.0 / beta;
             }
+            // The next step reads these at once: a wave without rows has no product to
+            // do first.  (Nobody reads them between the last exchange and here.)
+            __syncthreads();
             if (k == 0) {
                 e0 = alpha + I.eshift;
                 residual = beta / fmax(fabs(e0), 1e-3 * I.dscale);
