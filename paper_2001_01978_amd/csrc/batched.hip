@@ -710,6 +710,12 @@ std::vector<int> cost_order(int count, const int *omega, const int *n, int krylo
     return order;
 }
 
+// Krylov columns and two more vectors of an instance of d states.
+int64_t slot_for(int krylov, int64_t d) {
+    const int64_t m = std::min<int64_t>(krylov, d), ld = (d + 63) & ~int64_t(63);
+    return ((m + 2) * ld + 31) & ~int64_t(31);
+}
+
 Layout layout_for(int count, const int *omega, const int *n, int krylov) {
     Layout L;
     int64_t dmax = 1;
@@ -719,10 +725,6 @@ Layout layout_for(int count, const int *omega, const int *n, int krylov) {
         L.occ_doubles += omega[i];
     }
     L.m_max = (int)std::min<int64_t>(krylov, dmax);
-    auto slot_for = [krylov](int64_t d) {
-        const int64_t m = std::min<int64_t>(krylov, d), ld = (d + 63) & ~int64_t(63);
-        return ((m + 2) * ld + 31) & ~int64_t(31);
-    };
     // The whole device when teams are planned (a few large instances still
     // fill every compute unit); one workgroup per instance otherwise.
     L.grid = device_cus();
@@ -735,9 +737,9 @@ Layout layout_for(int count, const int *omega, const int *n, int krylov) {
     int64_t d1 = 0, d2 = 0;
     for (int q = n_large; q < n_teams; ++q) d1 = std::max(d1, dim_of(q));
     for (int q = n_teams; q < count; ++q) d2 = std::max(d2, dim_of(q));
-    L.slot_doubles = n_large > 0 ? slot_for(dmax) : 0;
-    L.mid_doubles = d1 > 0 ? slot_for(d1) : 0;
-    L.slot2_doubles = d2 > 0 ? slot_for(d2) : 0;
+    L.slot_doubles = n_large > 0 ? slot_for(krylov, dmax) : 0;
+    L.mid_doubles = d1 > 0 ? slot_for(krylov, d1) : 0;
+    L.slot2_doubles = d2 > 0 ? slot_for(krylov, d2) : 0;
     size_t off = 0;
     L.inst = off;
     off += align256(sizeof(Instance) * (size_t)count);
@@ -918,19 +920,26 @@ pd_status batched_run(int count, const int *omega, const int *n, const double *e
         } else {
             auto ts = std::chrono::steady_clock::now();
             const int S = std::min(count, kSample);
+            // The sample runs on the largest teams there are (short trials); without
+            // teams, on single workgroups.  The slots of the teams of 8 hold the
+            // instances planned for them, the costliest ones: one further down the
+            // cost order may have more states (4 of 32 orbits and 3 pairs, 4960
+            // states, are costlier than 400 of 15 and 6, 5005) and then gives way to
+            // the next costlier one that fits.
+            const bool on_teams = plan.teams > 0 || plan.mid_teams > 0;
+            const int64_t slot = plan.teams > 0 ? L.slot_doubles : on_teams ? L.mid_doubles : L.slot2_doubles;
             std::vector<Instance> sample(S);
             for (int q = 0; q < S; ++q) {
                 // quantiles 5% .. 100% of the cost order (largest excluded)
                 int pos = (int)((double)(q + 1) / (S + 1) * (count - 1));
-                sample[q] = sorted[std::min(count - 1, pos + count / 20)];
+                pos = std::min(count - 1, pos + count / 20);
+                while (pos > 0 && slot_for(o->krylov, sorted[pos].dim) > slot) --pos;
+                sample[q] = sorted[pos];
             }
             PD_HIP(hipMemcpyAsync(d_sample, sample.data(), sizeof(Instance) * S, hipMemcpyHostToDevice, stream));
             Args As = A;
             As.inst = d_sample;
             As.count = S;
-            // The sample runs on the largest teams there are (short trials), whose
-            // slots hold every instance; without teams, on single workgroups.
-            const bool on_teams = plan.teams > 0 || plan.mid_teams > 0;
             As.level[0].end = plan.teams > 0 ? S : 0;
             As.level[1].end = on_teams ? S : 0;
             if (plan.teams > 0) As.level[1].teams = 0;

@@ -1,7 +1,9 @@
 // The batched solver (batched.hip) on the CPU: its kernel's code runs with one
-// fiber per lane and one host thread per workgroup.
+// fiber per lane and one host thread per workgroup, its host code runs over host
+// memory, and launches are looked at instead of made.
 //
 //   batched_host solve BLOCK TEAM SEED        one instance read from stdin
+//   batched_host tune                         a batch's shape read from stdin
 //
 // A wave runs until all of its lanes wait at a workgroup barrier, then another
 // one is chosen by SEED: 0 the first wave first, 1 the last wave first, else at
@@ -168,6 +170,26 @@ namespace pd {
 namespace batched {
 thread_local unsigned char bdyn[64 << 10];
 
+// Every instance that a launch may hand to a level has to fit that level's slots.
+static int g_launches, g_bad;
+static void look(const Args &A) {
+    ++g_launches;
+    for (int i = 0; i < A.count; ++i) {
+        const Instance &I = A.inst[i];
+        const int64_t need = (I.m + 2) * ((I.dim + 63) & ~int64_t(63));
+        const bool l0 = A.level[0].teams > 0 && i < A.level[0].end, l1 = A.level[1].teams > 0 && i < A.level[1].end;
+        const int64_t have = l0 ? A.level[0].slot_doubles : l1 ? A.level[1].slot_doubles : A.slot2_doubles;
+        if (need > have) {
+            ++g_bad;
+            std::printf("launch %d, instance %d of %d: %lld doubles in a slot of %lld\n", g_launches, i, A.count,
+                        (long long)need, (long long)have);
+        }
+        Result r = {};
+        r.converged = 1;
+        A.res[I.orig] = r;
+    }
+}
+
 struct Problem {
     int omega, n, krylov;
     double tol;
@@ -239,7 +261,9 @@ pd_status pack_coefficients(int, int, const double *, const double *, CoefBlock 
 }  // namespace pd
 
 template <typename F, typename... A>
-static void launched(F, A...) {}
+static void launched(F, A... args) {
+    if constexpr (sizeof...(A) == 1) pd::batched::look(args...);
+}
 
 // The HIP calls of the host code, over host memory.
 #define STUB(name, args) \
@@ -290,6 +314,32 @@ int main(int argc, char **argv) {
         for (double &v : P.d) if (std::scanf("%lf", &v) != 1) return 2;
         for (double &v : P.V) if (std::scanf("%lf", &v) != 1) return 2;
         pd::batched::solve(P, std::atoi(argv[2]), std::atoi(argv[3]), (unsigned)std::atoi(argv[4]));
+        return 0;
+    }
+    if (argc == 2 && !std::strcmp(argv[1], "tune")) {
+        int kinds, krylov;
+        std::vector<int> omega, n;
+        if (std::scanf("%d %d", &krylov, &kinds) != 2) return 2;
+        size_t ne = 0, nv = 0;
+        for (int k = 0, o, p, c; k < kinds; ++k) {
+            if (std::scanf("%d %d %d", &o, &p, &c) != 3) return 2;
+            for (int i = 0; i < c; ++i) {
+                omega.push_back(o), n.push_back(p);
+                ne += o, nv += (size_t)o * o;
+            }
+        }
+        const int count = (int)omega.size();
+        pd_lanczos_opts o = {};
+        o.krylov = krylov;
+        o.tol = 1e-10;
+        o.max_restarts = 10;
+        std::vector<unsigned char> work(pd::batched_workspace_bytes(count, omega.data(), n.data(), &o));
+        std::vector<double> eps(ne), V(nv), E0(count), occ(ne);
+        pd_batch_info info = {};
+        const pd_status st = pd::batched_run(count, omega.data(), n.data(), eps.data(), V.data(), &o, 0, work.data(),
+                                             work.size(), E0.data(), occ.data(), nullptr, &info, nullptr);
+        std::printf("status %d launches %d teams %d of %d tuned %d bad %d\n", (int)st, pd::batched::g_launches,
+                    info.teams, info.team_size, info.tuned, pd::batched::g_bad);
         return 0;
     }
     return 2;

@@ -45,3 +45,21 @@ def test_result_does_not_depend_on_the_order_of_the_waves(host, oracle_mod, om, 
     e0, _, occ0, _ = oracle_mod.dense_ground(om, n, eps, V)
     assert out[0][4] == "1" and abs(float(out[0][0]) - e0) <= 1e-10 * abs(e0)
     assert np.allclose([float(v) for v in out[0][5:]], occ0, atol=1e-8)
+
+
+@pytest.mark.parametrize("krylov,kinds", [
+    (20, [(32, 3, 4), (15, 6, 400)]),    # 4960 and 5005 states: the smaller ones are the costlier
+    (8, [(32, 3, 16), (15, 6, 220)]),
+    (2, [(32, 3, 16), (15, 6, 220)]),
+    (20, [(16, 8, 64)]),                 # teams of 8 only, all alike
+    (20, [(22, 11, 6), (12, 6, 100)]),   # large teams
+    (20, [(10, 5, 300)]),                # single workgroups
+])
+def test_every_launch_fits_its_slots(host, krylov, kinds):
+    """The tuner's trials and the solve: an instance goes to a level whose slots
+    hold its Krylov vectors."""
+    text = f"{krylov} {len(kinds)} " + " ".join(f"{o} {n} {c}" for o, n, c in kinds)
+    r = subprocess.run([host, "tune"], input=text, capture_output=True, text=True, timeout=120)
+    last = r.stdout.splitlines()[-1].split()
+    assert r.returncode == 0 and last[:4] == ["status", "0", "launches", "4"], r.stdout
+    assert last[-2:] == ["bad", "0"], r.stdout
