@@ -425,8 +425,10 @@ constexpr double kReorthTau2 = (1.0 / 128.0) * (1.0 / 128.0);
 
 // v = beta q_{k+1}.  A vanished v (an invariant subspace: the host ends the cycle
 // there) gets scale 0, so that the steps already queued behind it stay finite.
+// The norm of a product that overflowed is NaN and stays NaN (fmax would make it a
+// vanished one): the host's tridiagonal solver refuses it.
 __device__ __forceinline__ void step_norm(const LanczosStep &st, double nrm_v) {
-    const double beta = sqrt(fmax(nrm_v, 0.0));
+    const double beta = nrm_v < 0.0 ? 0.0 : sqrt(nrm_v);
     double tnorm = 0.0;
     for (int i = 0; i < st.k; ++i) tnorm = fmax(tnorm, fabs(st.s->alpha[i]) + st.s->beta[i]);
     tnorm = fmax(tnorm, fabs(st.s->alpha[st.k]) + beta);
