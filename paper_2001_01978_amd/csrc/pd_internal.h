@@ -220,13 +220,14 @@ hipError_t launch_basis_unrank(int omega, int n, const int64_t *ranks, int64_t c
 constexpr int kMaxSigmaPairs = 20;
 // Full-space products refused: mirrored spaces (n > omega - n) with 16 pairs
 // in the working space and 32-bit ranks, i.e. omega 33, 34, 35 with n = omega
-// - 16.  Their FP64 kernel (the library's only kernel that uses scratch: it
-// spills 20-24 bytes per lane) made an illegal memory access on the device at omega = 34,
-// n = 18, and the cause is not found: the row code, compiled for the host with
-// every array it reads against an inaccessible page, touches nothing outside
-// them on any row of the three spaces, so what remains is the compiled kernel
-// or its launch.  They stay refused until the cause is shown.  Truncated
-// products are not affected.
+// - 16.  The row-per-lane FP64 kernel that they took (the only product kernel that
+// used scratch: it spilled 20-24 bytes per lane) made an illegal memory access
+// on the device at omega = 34, n = 18, and the cause was not found: the row code,
+// compiled for the host with every array it reads against an inaccessible
+// page, touches nothing outside them on any row of the three spaces.  That kernel is
+// no longer built, as every other space of its kind goes by windows, and these
+// would too; but they have run on no device since, and stay refused until the cause is
+// shown.  Truncated products are not affected.
 inline bool sigma_space_refused(int omega, int n) {
     const int nn = omega - n;
     return n > nn && nn == 16 && binom_host(omega, n) < (uint64_t(1) << 32);

@@ -347,14 +347,10 @@ __device__ __forceinline__ T sigma_row(int64_t row, int64_t dim, int omega, int 
 }
 
 // With at most 17 pairs the product keeps all NN gathers of a hop block in
-// flight (ISSUE_ALL).  32-bit ranks: within 128 VGPRs, so 4 waves per SIMD,
-// the occupancy the LDS allows (measured at 32 and 34 orbits: 6-11% faster in
-// FP64, 7-9% in FP32; mirrored, 32 orbits and 17 pairs: 91.6 -> 79.8 ms
-// FP64).  The mirrored FP64 kernel at 16 pairs spills 20-24 bytes per lane
-// there; a copy of it outside the library ran 34 orbits, 18 pairs in 363
-// against 515 ms, but the library's spaces that use it are refused
-// (sigma_space_refused: an unexplained illegal memory access).  64-bit ranks: 3 waves
-// per SIMD, without spills when not mirrored (35 orbits, 17 pairs: 1557 ->
+// flight (ISSUE_ALL).  32-bit ranks (at most 11 pairs, full_pairs): within 128
+// VGPRs, so 4 waves per SIMD, the occupancy the LDS allows (6-11% faster in FP64
+// and 7-9% in FP32 at 16 and 17 pairs, spaces that go by windows now).  64-bit ranks: 3 waves
+// per SIMD, without spills when not mirrored (35 orbits, 17 pairs, then: 1557 ->
 // 1348 ms FP64, 803 -> 700 ms FP32); mirrored they spill up to 188 bytes per
 // lane and ran 2.3-3.2x slower, so they keep the compiler's schedule.
 template <typename R, bool COMP, int NN>
@@ -481,7 +477,6 @@ __global__ __launch_bounds__(BLOCK, (sigma_min_waves<R, COMP, NN>())) void sigma
 // a row are no faster at any size (352,716 states: 30 / 52 / 72 us).
 constexpr int64_t kSmallDim = int64_t(1) << 22;
 constexpr int kSmallBlock = 256;
-constexpr int kSmallPairs = 12;   // C(25, 13) > kSmallDim
 template <typename R, typename T, int NN, bool COMP, bool BUF>
 __global__ __launch_bounds__(kSmallBlock) void sigma_small_kernel(Params<R, T> P) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -502,9 +497,12 @@ __global__ __launch_bounds__(kSmallBlock) void sigma_small_kernel(Params<R, T> P
                                                            kSmallBlock, xr);
 }
 
-template <typename R, typename T, int NN>
-constexpr bool sigma_small_pairs() {
-    return sizeof(R) == 4 && NN <= kSmallPairs;
+// Most pairs of a full space that takes a row per lane.  With 32-bit ranks 11: a space of
+// 12 or more has at least C(24, 12) = 2.7e6 states, and at most 40 orbits (C(41,
+// 12) > 2^32), so its products go by windows.
+template <typename R>
+constexpr int full_pairs() {
+    return sizeof(R) == 4 ? 11 : kMaxSigmaPairs;
 }
 
 // Dynamic LDS limit to set on an instantiation with NN pairs and BLOCK
@@ -566,7 +564,7 @@ LaunchShape choose_shape(int omega, int ks) {
 
 template <typename R, typename T, int NN, bool COMP>
 hipError_t launch_nn(const Params<R, T> &P, hipStream_t stream) {
-    if constexpr (sigma_small_pairs<R, T, NN>()) {
+    if constexpr (sizeof(R) == 4) {
         if (P.dim < kSmallDim) {
             constexpr bool kBuf = sizeof(T) == 4;
             const size_t smem = ((table_bytes<R, T>(P.omega, P.ks) + 15) & ~size_t(15)) + prefix_bytes<R>(NN, kSmallBlock);
@@ -607,15 +605,18 @@ bool shape_for(int omega, int nn, LaunchShape *out) {
 template <typename R, typename T, bool COMP>
 hipError_t dispatch_nn(const Params<R, T> &P, hipStream_t stream) {
     switch (P.nn) {
-#define PD_NN_CASE(K) \
-    case K: return launch_nn<R, T, K, COMP>(P, stream);
+#define PD_NN_CASE(K)                                                                   \
+    case K:                                                                             \
+        if constexpr (K <= full_pairs<R>()) return launch_nn<R, T, K, COMP>(P, stream); \
+        break;
         PD_NN_CASE(0) PD_NN_CASE(1) PD_NN_CASE(2) PD_NN_CASE(3) PD_NN_CASE(4) PD_NN_CASE(5) PD_NN_CASE(6)
         PD_NN_CASE(7) PD_NN_CASE(8) PD_NN_CASE(9) PD_NN_CASE(10) PD_NN_CASE(11) PD_NN_CASE(12) PD_NN_CASE(13)
         PD_NN_CASE(14) PD_NN_CASE(15) PD_NN_CASE(16) PD_NN_CASE(17) PD_NN_CASE(18) PD_NN_CASE(19)
         PD_NN_CASE(20)
 #undef PD_NN_CASE
-        default: return hipErrorInvalidValue;
+        default: break;
     }
+    return hipErrorInvalidValue;
 }
 
 // Truncated space: row i is the state of full rank kranks[i]; static tile
