@@ -95,7 +95,9 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = ["paper_2001_01978_amd/csrc/window_impl.h"]
+#: the windowed product: its kernels and launches, and the plan that cuts the space for them
+KERNEL_SOURCES = ["paper_2001_01978_amd/csrc/" + f for f in
+                  ("window_impl.h", "window_plan.h", "window_plan.cpp", "window_f32.hip", "window_f64.hip")]
 COUNTERS = "sigma_omega{om}_n{n}_counters"
 PIPELINE = "sigma_omega{om}_n{n}_pipeline_counters"
 CLOCK_HZ, N_CU, N_SIMD = 2.4e9, 256, 1024
