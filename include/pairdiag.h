@@ -157,17 +157,21 @@ pd_status pd_basis_truncation(pd_basis b, int *truncated, int64_t *full_dim);
  * symmetric and finite.  x, y: device vectors of dim elements of dtype dt
  * (PD_F64: double gathers and accumulation; PD_F32: float gathers, float
  * accumulation, coefficients rounded to float).  x and y must not overlap.
- * The handle's device buffer holds 4 coefficient blocks, each with the
+ * The handle's device buffer holds 5 coefficient blocks, each with the
  * kernel's tile counters.  A call takes a block that is unused, or
  * was last used on the same stream (stream order protects it), or whose last
  * product has finished; if every block is busy on other streams, `stream`
  * first waits for the oldest one's product.  So concurrent calls on one
  * handle from different streams and host threads are allowed and each
- * returns the complete product (at most 4 of them run truly in parallel).
+ * returns the complete product (at most 5 of them run truly in parallel).
+ * While one stream alone uses a handle no event is recorded behind its products;
+ * its block stays that stream's until it calls again beside another stream (4
+ * blocks are left to the others until then).
  * When the coefficients differ from those the chosen block holds they are
- * uploaded on `stream` and the stream is synchronised; otherwise the call is
- * fully asynchronous.  pd_lanczos_ground keeps its own block in its
- * workspace.
+ * uploaded on `stream` and the stream is synchronised, and the first product or
+ * solve of a handle whose space goes by windows uploads that plan in the
+ * same way; otherwise the call is fully asynchronous.  pd_lanczos_ground keeps
+ * its own block in its workspace.
  * PD_ERANGE, before any device work: min(n, omega - n) above 20; or a full
  * space with n = omega - 16 and omega 33, 34 or 35 (mirrored, 16 pairs,
  * 32-bit ranks), whose product is disabled: it made an illegal memory access

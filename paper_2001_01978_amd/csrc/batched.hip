@@ -5,8 +5,8 @@
 // longest-processing-time order) and runs the whole restarted Lanczos
 // iteration of Sec. 3.4 for it: the product (the same per-row hop code as
 // the single-instance sigma, with its per-lane slots in dynamic LDS), Gram-Schmidt against all stored vectors
-// (a second pass only when needed), the tridiagonal eigensolver (bisection + inverse
-// iteration, one lane), the restart, the convergence test of Eq. convergence
+// (a second pass only when needed), the tridiagonal eigensolver (multisection by the 64
+// lanes of a wave, inverse iteration by one), the restart, the convergence test of Eq. convergence
 // and the occupation numbers -- all without returning to the host.  The
 // Krylov vectors of an instance live in a per-workgroup slot of the caller's
 // workspace and stay in L2 / the Infinity Cache for all but the largest

@@ -126,9 +126,10 @@ __device__ __forceinline__ T buffer_gather(__amdgpu_buffer_rsrc_t rs, uint32_t b
 //   MAP 3, 4 (32-bit ranks): one 4-byte cell per 16 full ranks (kept bits,
 //          kept count since the start of its block of 2^16 ranks) and the blocks'
 //          counts, which MAP 3 has in LDS: row = block + cell + popcount(bits below).
-// A hop is bound by the texture addresser: 8 cycles for a wave's cells and 16 to 20
-// for its elements where MAP 1's words take another 16, and 10 instead of 25 VALU
-// instructions.  The elements of dropped targets are loaded too (a neighbour's)
+// A hop takes two loads (three with MAP 4) of 8 to 12 addresser cycles, where MAP 1's two
+// take 17 to 20 each, and 24 to 26 VALU instructions, as before.  Busy, VALU / texture
+// addresser: MAP 3 at 28 orbits 0.87 / 0.82 in FP64 and 0.92 / 0.71 in FP32, MAP 4 at
+// 32 orbits 0.67 / 0.88 and 0.79 / 0.79.  The elements of dropped targets are loaded too (a neighbour's)
 // and replaced by 0 afterwards: a branch around each load kept them from being
 // in flight together.  1e7 of 4.0e7 states (28 orbits), FP64: 2289 us with MAP 1,
 // 1848 with cells, 1546 without the branches.  MAP 4 asks for the blocks' counts

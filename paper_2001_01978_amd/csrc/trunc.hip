@@ -251,8 +251,7 @@ __global__ __launch_bounds__(kT) void scan_add_kernel(TruncWord *words, int64_t 
         if (w0 + k < W) words[w0 + k].base += off;
 }
 
-// kranks holds `cap` entries; a selection that keeps more (a caller's info
-// that does not match the cut) writes none past it and is rejected afterwards.
+// Kept ranks before each block of 2^kSuperBits ranks: the base of its first word.
 __global__ __launch_bounds__(kT) void supers_kernel(const TruncWord *words, int64_t count, uint32_t *supers) {
     for (int64_t b = blockIdx.x * (int64_t)kT + threadIdx.x; b < count; b += (int64_t)gridDim.x * kT)
         supers[b] = (uint32_t)words[b << (kSuperBits - 6)].base;
@@ -274,6 +273,8 @@ __global__ __launch_bounds__(kT) void cells_kernel(TruncWord *words, int64_t W, 
     }
 }
 
+// kranks holds `cap` entries; a selection that keeps more (a caller's info
+// that does not match the cut) writes none past it and is rejected afterwards.
 template <typename R>
 __global__ __launch_bounds__(kT) void ranks_kernel(const TruncWord *words, int64_t W, R *kranks, uint64_t cap) {
     for (int64_t w = blockIdx.x * (int64_t)kT + threadIdx.x; w < W; w += (int64_t)gridDim.x * kT) {

@@ -487,9 +487,9 @@ hipError_t finalize(const double *partials, unsigned nb, int ncols, double scale
         else if ((ncols) <= 48) hipLaunchKernelGGL(KERNEL<48>, __VA_ARGS__);                     \
         else hipLaunchKernelGGL(KERNEL<64>, __VA_ARGS__);                                        \
     } while (0)
-// Same, for kernels templated on the column bound and the input type.  20 is the
-// default cycle: with 24 slots its last steps load 4 columns twice (80 against 85 us
-// at 24 orbits).
+// Same, for kernels templated on the column bound and the input type.  20 is a common
+// cycle (the batched solver's default and the benchmark's; pd_lanczos_ground's is 50): with
+// 24 slots its last steps load 4 columns twice (80 against 85 us at 24 orbits).
 #define PD_DISPATCH_COLS_T(ncols, T, KERNEL, ...)                                                 \
     do {                                                                                         \
         if ((ncols) <= 4) hipLaunchKernelGGL((KERNEL<4, T>), __VA_ARGS__);                       \
