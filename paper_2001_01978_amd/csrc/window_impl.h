@@ -27,7 +27,9 @@
 // and the segments 4.9.  The windows are bound by the address path of the L1: 26 and
 // 18 loads per row and 27 and 25 cycles per load (a contiguous 8-byte load of 64
 // lanes takes 16), 85% and 80% of the time; at the same time 65 and 26 GB come from below
-// the L2s, 5 and 3 TB/s.  The arithmetic alone would take 4 ms.
+// the L2s, 5 and 3 TB/s.  The arithmetic alone would take 4 ms.  In FP32 (14.5 ms) no
+// unit is as busy, the addresser 66% and the VALU 46% of the time: three waves per SIMD
+// leave latency bare.
 #pragma once
 
 #include <type_traits>
@@ -849,7 +851,9 @@ __global__ __launch_bounds__(kSegThreads, sizeof(T) == 8 ? 2 : 4) void segment_k
 // A pass of fewer workgroups leaves wave slots empty (a CU holds two of W = 8 in
 // FP64): two waves then share the lanes of each.  24 orbits, 12 pairs (257 workgroups): the
 // product takes 97.9 / 77.6 us (FP64 / FP32) so and 104 / 87 without; 23 orbits, 11 pairs
-// 66.7 / 54.4 and 71.8 / 60.3.  From 512 on, the slots are taken either way.
+// 66.7 / 54.4 and 71.8 / 60.3.  From 512 on, the slots are taken either way.  Built for the
+// one window of 7 or 8 of spaces of 23 (11, 12 pairs) and 24 orbits (11 to 13); smaller ones take
+// a row per lane, larger ones have more workgroups, and windows of 5 and 6 with it are untried.
 constexpr uint32_t kSplitBlocks = 512;
 
 template <typename T, int W>

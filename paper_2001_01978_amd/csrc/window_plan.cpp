@@ -11,7 +11,8 @@ namespace {
 constexpr int kMinW = 4, kMaxW = 8;
 constexpr int kWinBlock = 256;
 constexpr uint64_t kMinGroups = 512;       // two for each CU
-// At 24 orbits, one window of 8 from here on and two of 4 below: 24 orbits, 9 pairs (1.3e6
+// Eight orbits above the segments can be one window or two (fewer cannot be two, more are
+// two at least): one of 8 from here on, two of 4 below: 24 orbits, 9 pairs (1.3e6
 // states) 78.6 / 58.3 us (FP64 / FP32) with two and 92.9 / 72.8 with one; 10 pairs (2.0e6)
 // 93.5 / 74.8 and 94.1 / 74.4; 12 pairs (2.7e6) 120 / 90 and 97.8 / 77.7.
 constexpr uint64_t kMinWideDim = 2000000;
